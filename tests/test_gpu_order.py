@@ -1,0 +1,83 @@
+"""The two ways a queue of more than 1024 requests is ordered (tiled sort,
+radix sort) against the oracle, where each can go wrong: the sizes at which
+the tile size or the way changes, keys too wide for the tiled sort, queues
+already in order, and a bucket of more keys than a workgroup sorts in LDS.
+All integers: exact."""
+import numpy as np
+import pytest
+import torch  # noqa: F401  (imported at collection: the first import is slow)
+
+from tests import helpers
+from tests.test_gpu_parity import assert_same, dev, run_both  # noqa: F401  (dev: fixture)
+
+pytestmark = pytest.mark.gpu
+
+
+def queued(n, elapsed, slo_s=600):
+    """n queued requests of one class, alike but for their waits: the order
+    is that of the waits, longest first."""
+    import paper_2608_06557_amd.synth as synth
+    w = synth.make_workload(0, n=1)
+    for k in ["slo_class", "state", "queue_tier", "prefix_tier", "n_in", "n_out_pred",
+              "n_prefix", "n_progress"]:
+        w[k] = np.repeat(w[k][:1], n)
+    w["state"][:] = helpers.QUEUED
+    w["n_progress"][:] = 0
+    w["params"]["slo_ns"] = [slo_s * 10 ** 9] * 3 + [0] * 13
+    w["arrival_ns"] = w["params"]["t_now_ns"] - np.asarray(elapsed, np.int64)
+    w["id"] = np.arange(n, dtype=np.uint64) * 3 + 5
+    w["row_offsets"] = np.zeros(n + 1, np.int32)
+    w["slots"] = np.zeros(0, np.int32)
+    return w
+
+
+# 256-, 512- and 1024-request tiles, full and short, and the radix sort above
+@pytest.mark.parametrize("n", [1025, 1279, 1281, 65536, 65537, 65281, 131072, 131073, 131585,
+                               262143, 262144, 262145])
+def test_tile_size_edges(dev, n):  # noqa: F811
+    import paper_2608_06557_amd.synth as synth
+    w = synth.make_workload(3 if n < 100000 else 4, seed=n, n=n)
+    g, o = run_both(dev, w)
+    assert_same(g, o, f"n={n}")
+
+
+# stamps of a wall clock in ns: key and index need more than one word
+@pytest.mark.parametrize("n", [1025, 16384, 16385, 65537])
+def test_wide_keys_take_the_radix_sort(dev, n):  # noqa: F811
+    import paper_2608_06557_amd.synth as synth
+    w = synth.make_workload(2, seed=n, n=n)
+    shift = 1_700_000_000_000_000_000 - w["params"]["t_now_ns"]
+    w["params"]["t_now_ns"] += shift
+    w["arrival_ns"] = w["arrival_ns"] + shift
+    g, o = run_both(dev, w)
+    assert_same(g, o, f"n={n}")
+
+
+@pytest.mark.parametrize("how", ["ascending", "descending", "few"])
+def test_ordered_and_repeated_waits(dev, how):  # noqa: F811
+    """Queues in arrival order (a bucket is one tile's) and of 40 waits."""
+    n = 70000
+    rng = np.random.default_rng(3)
+    e = {"ascending": np.arange(n) * 1000, "descending": np.arange(n)[::-1] * 1000,
+         "few": rng.integers(0, 40, n) * 10 ** 9}[how]
+    g, o = run_both(dev, queued(n, e))
+    assert_same(g, o, how)
+
+
+@pytest.mark.parametrize("pos", [0, 1])
+def test_bucket_beyond_lds(dev, pos):  # noqa: F811
+    """63 of each tile's 1024 keys lie between two of its sampled places (64
+    apart from place 7 * tile mod 64) and in one range over all tiles, so no
+    sample splits that range: 16128 keys in one bucket."""
+    n, T = 262144, 1024
+    rng = np.random.default_rng(11 + pos)
+    wait = np.zeros(n, np.int64)
+    for t in range(n // T):
+        first = (7 * t) % 64 + 64 * (7 * pos) + 1     # first place behind a sample
+        v = np.empty(T, np.int64)
+        v[:first] = rng.integers(200, 300, first)      # least budget: longest wait
+        v[first:first + 63] = rng.integers(100, 130, 63)  # ties across all tiles
+        v[first + 63:] = rng.integers(0, 50, T - first - 63)
+        wait[t * T:(t + 1) * T] = rng.permutation(v)
+    g, o = run_both(dev, queued(n, wait * 10 ** 9))
+    assert_same(g, o, "overflow")
