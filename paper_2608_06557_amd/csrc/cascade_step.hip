@@ -400,14 +400,14 @@ struct KeySpec {
   unsigned long long lo, span;  // lowest biased budget, budgets per group
   int idx_bits;
 };
-constexpr int kSampled = 16;    // keys sampled from every sorted tile
-
-// Sampled places of a sorted tile of T keys: j * (T / kSampled) + the tile's
-// offset.  The offset differs from tile to tile, so that tiles holding the
+// Keys sampled from every sorted tile of T keys, at the places j * (T /
+// samples) + the tile's offset.  A bucket's size strays by about 0.3 * (T /
+// samples) * sqrt(tiles) keys, so large tiles take more.  The offset differs from tile to tile, so that tiles holding the
 // same budgets do not all sample the same few of them.
+constexpr int samples_of(int T) { return T > 512 ? 32 : 16; }
 template <int T>
 __device__ __forceinline__ int sample_offset(int tile) {
-  return (tile * 7) & (T / kSampled - 1);
+  return (tile * 7) & (T / samples_of(T) - 1);
 }
 
 // One lane per request; with kTiled the workgroup's requests are a tile,
@@ -523,6 +523,7 @@ __global__ __launch_bounds__(NW * 64) void eval_kernel(
   if (kTiled) {
     const unsigned long long *run = merge_runs<T>(s_run[0], s_run[1], T);
     if (i < n) keys[i] = run[threadIdx.x];  // a short tile's padding sorts behind its keys
+    constexpr int kSampled = samples_of(T);
     if (threadIdx.x < kSampled)
       samples[(size_t)threadIdx.x * gridDim.x + blockIdx.x] =
           run[threadIdx.x * (T / kSampled) + sample_offset<T>((int)blockIdx.x)];
@@ -1098,58 +1099,65 @@ __global__ __launch_bounds__(kSortBlock) void radix_pass_kernel(
 // --------------------------------------------------------- tiled sort
 
 // The order of a queue of up to kTiledMax requests whose keys fit one word
-// (key and index): eval leaves every tile of T requests sorted, with kSampled
+// (key and index): eval leaves every tile of T requests sorted, with some
 // of its keys sampled; split_kernel ranks all samples and takes every
-// kSampled-th as a splitter; bucket_kernel gives each workgroup the keys
+// `per`-th as a splitter; bucket_kernel gives each workgroup the keys
 // between two splitters, from every tile, sorts them and writes its run of
 // the order.  Three dependent launches (with eval) where the radix sort has
 // seven (eval, prep, one per digit), and nothing in them waits on another
 // workgroup.  There are as many buckets as tiles (p <= kTiledTiles); a bucket
-// holds about T keys, and never more than (p + kSampled) * T / kSampled.  Both
+// holds about T keys, and never more than its samples' gaps and one gap more
+// per tile.  Both
 // sorts are chains of round trips through memory, so fewer launches win: the
-// whole step takes 47.8 us instead of 61.7 at 8192 requests, 56.9 instead of
-// 77.7 at 65536 and 85.3 instead of 122.1 at 262144.  Beyond, a tile would
+// whole step takes 43.4 us instead of 61.7 at 8192 requests, 49.7 instead of
+// 77.7 at 65536 and 80.4 instead of 122.1 at 262144.  Beyond, a tile would
 // need more than 1024 threads or the samples more than split's registers.
 constexpr int kTiledTiles = 256;
 constexpr int kTiledMax = kTiledTiles * 1024;
+// Threads of a bucket's workgroup: twice its usual keys where that fits, so
+// that few buckets need a second key per thread.
+constexpr int bucket_threads(int T) { return T == 256 ? 512 : 1024; }
+constexpr int kOwnSamples = 16;  // samples that a split workgroup ranks
 constexpr int kBucketCap = 4352;  // keys a bucket sorts in LDS: all it can hold for T = 256
-static_assert(kBucketCap >= (kTiledTiles + kSampled) * 256 / kSampled, "every T = 256 bucket");
+static_assert(kBucketCap >= (kTiledTiles + samples_of(256)) * 256 / samples_of(256), "its bound");
 
-// Ranks every sample against all of them (each workgroup its tile's own, by
-// wave ballots over the 16 samples each lane holds) and stores the splitters;
+// Ranks every sample against all of them (each workgroup kOwnSamples, by
+// wave ballots over the kS samples each thread holds) and stores the splitters;
 // also reduces eval's partials and checks the block-table slots, whose extent
 // is only trustworthy after eval.
+template <int kS>
 __global__ __launch_bounds__(kBlock) void split_kernel(
     int n, int num_blocks, int p, const Partial *__restrict__ partials,
     const int *__restrict__ ro, const int *__restrict__ slots, Ctl *ctl, int *info,
-    const unsigned long long *__restrict__ samples, unsigned long long *__restrict__ splitters) {
-  static_assert(kTiledTiles <= kBlock, "all samples are kSampled per thread");
+    const unsigned long long *__restrict__ samples, int per,
+    unsigned long long *__restrict__ splitters) {
+  static_assert(kTiledTiles <= kBlock, "all samples are kS per thread");
   __shared__ unsigned long long s_red[kWaves * 9];
-  __shared__ unsigned s_below[kWaves][kSampled];
-  const int t = threadIdx.x, g = (int)blockIdx.x, count = p * kSampled;
-  unsigned long long v[kSampled], own[kSampled];
+  __shared__ unsigned s_below[kWaves][kOwnSamples];
+  const int t = threadIdx.x, g = (int)blockIdx.x, count = p * kS;
+  unsigned long long v[kS], own[kOwnSamples];
 #pragma unroll
-  for (int u = 0; u < kSampled; ++u) {
+  for (int u = 0; u < kS; ++u) {
     const int j = t + u * kBlock;
     v[u] = j < count ? samples[j] : ~0ull;  // never below a sample
   }
 #pragma unroll
-  for (int j = 0; j < kSampled; ++j) own[j] = samples[(size_t)j * p + g];
+  for (int j = 0; j < kOwnSamples; ++j) own[j] = samples[g * kOwnSamples + j];
   EvalTotals tot;
   const bool bad_data = eval_totals(p, partials, ctl, info, s_red, tot);
 
   // block-table slots: requested here, checked after the ranks
   const int nnz = bad_data ? 0 : ro[n];
-  const int gt = g * kBlock + t, gs = p * kBlock;
+  const int gt = g * kBlock + t, gs = (int)gridDim.x * kBlock;
   int sv[8];
 #pragma unroll
   for (int u = 0; u < 8; ++u) sv[u] = (gt + u * gs < nnz) ? slots[gt + u * gs] : 0;
 
 #pragma unroll
-  for (int j = 0; j < kSampled; ++j) {
+  for (int j = 0; j < kOwnSamples; ++j) {
     unsigned below = 0;
 #pragma unroll
-    for (int u = 0; u < kSampled; ++u)
+    for (int u = 0; u < kS; ++u)
       below += (unsigned)__builtin_popcountll(__ballot(v[u] < own[j]));
     if (lane_id() == 0) s_below[wave_id()][j] = below;
   }
@@ -1167,29 +1175,40 @@ __global__ __launch_bounds__(kBlock) void split_kernel(
   if (__syncthreads_or(bad ? 1 : 0)) {
     if (t == 0) set_status(info, CASCADE_EINVAL);
   }
-  if (t < kSampled) {
+  if (t < kOwnSamples) {
     unsigned rank = 0;
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) rank += s_below[w][t];
-    if (rank % kSampled == 0) splitters[rank / kSampled] = samples[(size_t)t * p + g];
+    if (rank % per == 0) splitters[rank / per] = samples[g * kOwnSamples + t];
   }
 }
 
+// Workgroups go to the kXcds XCDs in turn; this numbering gives each XCD a
+// contiguous range of the G values, so that what neighbours share is fetched
+// into one XCD's L2 only.
+constexpr int kXcds = 8;
+__device__ __forceinline__ int xcd_contiguous(int block, int G) {
+  const int x = block % kXcds, q = G / kXcds, r = G % kXcds;
+  return x * q + min(x, r) + block / kXcds;
+}
+
 // Bucket b: the keys from splitter b (the lowest key for b = 0) up to splitter
-// b + 1.  A tile's samples below a splitter leave fewer than T / kSampled of
+// b + 1.  A tile's samples below a splitter leave less than one gap of
 // its keys in question, which as many lanes read at once: one round trip for
-// the bucket's bounds in every tile.  The bucket's first place in the order is
-// the number of keys below its lower splitter.
-template <int NW>
-__global__ __launch_bounds__(NW * 64) void bucket_kernel(
+// the bucket's bounds in every tile (loads under branches took one each: 6 us
+// instead of 2.5).  The bucket's first place in the order is the number of
+// keys below its lower splitter.
+template <int T>
+__global__ __launch_bounds__(bucket_threads(T)) void bucket_kernel(
     int n, int p, int idx_bits, int *info, const unsigned long long *__restrict__ keys,
     const unsigned long long *__restrict__ samples,
     const unsigned long long *__restrict__ splitters, const int4 *__restrict__ rec, Sorted srt,
     unsigned *__restrict__ l1_tot, unsigned *share_lead) {
-  constexpr int T = NW * 64, kGap = T / kSampled, kGroups = 64 / kGap;
+  constexpr int kSampled = samples_of(T), kGap = T / kSampled, kGroups = 64 / kGap;
+  constexpr int N = bucket_threads(T), NW = N / 64;
   constexpr int kMost = (kTiledTiles + kSampled) * T / kSampled;  // keys of a bucket
   constexpr int kL1Tiles = kMost / kScanTile + 2;
-  static_assert(kGap >= 16 && kGap <= 64 && kTiledTiles <= T, "a lane group per bound");
+  static_assert(kGap >= 16 && kGap <= 64 && kTiledTiles <= N, "a lane group per bound");
   __shared__ unsigned long long s_a[kBucketCap], s_b[kBucketCap];
   __shared__ int s_first[2 * kTiledTiles];  // first key in question, per bound and tile;
                                             // then the bound itself
@@ -1197,11 +1216,12 @@ __global__ __launch_bounds__(NW * 64) void bucket_kernel(
   __shared__ int s_scan[NW * 2];
   __shared__ unsigned s_l1[kL1Tiles * kL1];
   __shared__ int s_bad;
-  const int t = threadIdx.x, lane = lane_id(), wave = wave_id(), b = (int)blockIdx.x;
+  const int t = threadIdx.x, lane = lane_id(), wave = wave_id();
+  const int b = xcd_contiguous((int)blockIdx.x, (int)gridDim.x);
   if (t == 0) s_bad = bad_status(load_agent(info));
   const unsigned long long lo_key = b > 0 ? splitters[b] : 0ull;
-  const unsigned long long hi_key = b + 1 < p ? splitters[b + 1] : ~0ull;
-  for (int k = t; k < kL1Tiles * kL1; k += T) s_l1[k] = 0;
+  const unsigned long long hi_key = b + 1 < (int)gridDim.x ? splitters[b + 1] : ~0ull;
+  for (int k = t; k < kL1Tiles * kL1; k += N) s_l1[k] = 0;
   if (t < p) {
     int c0 = 0, c1 = 0;
 #pragma unroll
@@ -1217,34 +1237,41 @@ __global__ __launch_bounds__(NW * 64) void bucket_kernel(
   __syncthreads();
   if (s_bad) return;  // a failed step: the scan reports it
   // the keys in question: a group of kGap lanes per (bound, tile); the next
-  // sampled key (not below the splitter) or the tile's end closes the range
-  constexpr int kBatch = 8;
+  // sampled key (not below the splitter) or the tile's end closes the range.
+  // No load sits under a branch, so that a batch's are all in flight together.
   const int li = lane % kGap, gi = lane / kGap;
-  for (int e0 = wave * kGroups + gi; e0 < 2 * p; e0 += kBatch * NW * kGroups) {
-    unsigned long long v[kBatch];
-    int first[kBatch];
+  auto bounds = [&](auto batch) {
+    constexpr int kBatch = decltype(batch)::value;
+    for (int e0 = wave * kGroups + gi; e0 - gi < 2 * p; e0 += kBatch * NW * kGroups) {
+      unsigned long long v[kBatch];
+      int first[kBatch];
+      bool ask[kBatch];
 #pragma unroll
-    for (int u = 0; u < kBatch; ++u) {
-      const int e = e0 + u * NW * kGroups;
-      v[u] = ~0ull;
-      first[u] = 0;
-      if (e < 2 * p) {
-        const int tile = e < p ? e : e - p;
-        const int end = min(T, n - tile * T), off = sample_offset<T>(tile);
+      for (int u = 0; u < kBatch; ++u) {
+        const int e = min(e0 + u * NW * kGroups, 2 * p - 1);
+        const int tile = e < p ? e : e - p, base = tile * T;
+        const int end = min(T, n - base), off = sample_offset<T>(tile);
         first[u] = s_first[e];
-        const int stop = first[u] == 0 ? off : first[u] + kGap - 1;
+        const int stop = min(first[u] == 0 ? off : first[u] + kGap - 1, end);
         const int q = first[u] + li;
-        if (q < min(stop, end)) v[u] = keys[(size_t)tile * T + q];
+        ask[u] = q < stop;
+        v[u] = keys[base + (ask[u] ? q : 0)];
+      }
+#pragma unroll
+      for (int u = 0; u < kBatch; ++u) {
+        const int e = e0 + u * NW * kGroups;
+        const uint64_t below = __ballot(ask[u] && v[u] < (e < p ? lo_key : hi_key));
+        const uint64_t mine =
+            kGap == 64 ? below : (below >> (gi * kGap)) & ((1ull << (kGap & 63)) - 1);
+        if (li == 0 && e < 2 * p) s_first[e] = first[u] + __builtin_popcountll(mine);
       }
     }
-#pragma unroll
-    for (int u = 0; u < kBatch; ++u) {
-      const int e = e0 + u * NW * kGroups;
-      const uint64_t below = __ballot(v[u] < (e < p ? lo_key : hi_key));
-      const uint64_t mine = kGap == 64 ? below : (below >> (gi * kGap)) & ((1ull << (kGap & 63)) - 1);
-      if (li == 0 && e < 2 * p) s_first[e] = first[u] + __builtin_popcountll(mine);
-    }
-  }
+  };
+  constexpr int kFewBounds = 2, kBounds = 2 * kTiledTiles / (NW * kGroups);
+  if (2 * p <= kFewBounds * NW * kGroups)
+    bounds(std::integral_constant<int, kFewBounds>());
+  else
+    bounds(std::integral_constant<int, kBounds>());  // every bound in one round trip
   __syncthreads();
   // the bucket's segment of every tile, one behind the other
   int len = 0, lo = 0;
@@ -1254,7 +1281,7 @@ __global__ __launch_bounds__(NW * 64) void bucket_kernel(
     len = max(min(s_first[p + t], end) - lo, 0);
   }
   int v2[2] = {len, lo}, tot2[2];
-  block_exclusive_scan<2, int, NW>(v2, tot2, s_scan);
+  block_exclusive_scan<2, int, kTiledTiles / 64>(v2, tot2, s_scan);  // the others hold zeros
   const int m = tot2[0], start = tot2[1];
   if (t < p) {
     s_off[t] = v2[0];
@@ -1298,15 +1325,15 @@ __global__ __launch_bounds__(NW * 64) void bucket_kernel(
       wave_sort(key);
       if (q < m) s_a[q] = key;
     }
-    const unsigned long long *run = merge_runs<T>(s_a, s_b, m);
-    for (int q0 = 0; q0 < m; q0 += T) {
+    const unsigned long long *run = merge_runs<N>(s_a, s_b, m);
+    for (int q0 = 0; q0 < m; q0 += N) {
       const int q = q0 + t;
       place(q < m, start + q, q < m ? run[q] : 0ull);
     }
   } else {
     // more keys than LDS holds (tiles that sample between the same budgets):
     // every key's place is the number of keys below it, counted tile by tile
-    for (int q0 = 0; q0 < m; q0 += T) {
+    for (int q0 = 0; q0 < m; q0 += N) {
       const int q = q0 + t;
       const unsigned long long key = q < m ? key_at(q) : 0ull;
       int pos = start;
@@ -1326,7 +1353,7 @@ __global__ __launch_bounds__(NW * 64) void bucket_kernel(
   if (broken) set_status(info, CASCADE_EINTERNAL);
   __syncthreads();
   const int words = min((start + max(m, 1) - 1) / kScanTile - tile0 + 1, kL1Tiles) * kL1;
-  for (int k = t; k < words; k += T) {
+  for (int k = t; k < words; k += N) {
     const unsigned v = s_l1[k];
     if (v) atomicAdd(l1_tot + (size_t)tile0 * kL1 + k, v);
   }
@@ -3429,7 +3456,7 @@ int step_impl(const cascade_requests_t *rq, const cascade_block_table_t *bt,
     const int tiles = (n + T - 1) / T;
     // samples and splitters use the radix passes' status words
     auto *samples = reinterpret_cast<unsigned long long *>(ws + L.sort_status);
-    auto *splitters = samples + kTiledTiles * kSampled;
+    auto *splitters = samples + kTiledTiles * samples_of(1024);
     const size_t clear_off = L.ctl + offsetof(Ctl, done);
     const size_t clear_vec = (L.sort_status - clear_off) / 16;
     static_assert(offsetof(Ctl, done) % 16 == 0, "16-byte clears");
@@ -3440,12 +3467,14 @@ int step_impl(const cascade_requests_t *rq, const cascade_block_table_t *bt,
                        ctl, reinterpret_cast<uint4 *>(ws + clear_off), clear_vec, clear2,
                        clear2_vec, out->info, partials, out->budget_ns, out->queue_tier_out,
                        keys_a, rec, spec, samples);
-    hipLaunchKernelGGL(split_kernel, dim3(tiles), dim3(kBlock), 0, s, n, ts->num_blocks, tiles,
-                       partials, bt->row_offsets, bt->slots, ctl, out->info, samples, splitters);
-    hipLaunchKernelGGL(T == 256   ? bucket_kernel<4>
-                       : T == 512 ? bucket_kernel<8>
-                                  : bucket_kernel<16>,
-                       dim3(tiles), dim3(T), 0, s, n, tiles, spec.idx_bits, out->info, keys_a,
+    hipLaunchKernelGGL(T <= 512 ? split_kernel<samples_of(512)> : split_kernel<samples_of(1024)>,
+                       dim3(tiles * samples_of(T) / kOwnSamples), dim3(kBlock), 0, s, n,
+                       ts->num_blocks, tiles, partials, bt->row_offsets, bt->slots, ctl,
+                       out->info, samples, samples_of(T), splitters);
+    hipLaunchKernelGGL(T == 256   ? bucket_kernel<256>
+                       : T == 512 ? bucket_kernel<512>
+                                  : bucket_kernel<1024>,
+                       dim3(tiles), dim3(bucket_threads(T)), 0, s, n, tiles, spec.idx_bits, out->info, keys_a,
                        samples, splitters, rec, srt, l1_tot, share ? share_lead : nullptr);
   } else {
     // longer queues, and parameters that allow wider budgets: the radix sort.

@@ -5,8 +5,8 @@
 // exchanges are DPP moves (only the three exchanges that cross a row of 16
 // lanes go through the LDS crossbar).  A workgroup then merges the sorted
 // runs pairwise in LDS: every key finds its place in the other run of its
-// pair by a branch-free search, so a level costs log2(run) + 1 dependent LDS
-// reads and one barrier, whatever the keys are.  Both are bound by the
+// pair by a branch-free search, so a level costs about log2(run) / 2 dependent
+// LDS round trips and one barrier, whatever the keys are.  Both are bound by the
 // latency of that chain, not by the number of compares.
 #pragma once
 #include <hip/hip_runtime.h>
@@ -65,33 +65,79 @@ __device__ __forceinline__ void wave_sort(unsigned long long &k) {
       exchange<1>(k);
 }
 
-// Where key, at place q of m keys in sorted runs of L (a power of two; the
-// last run may be short), goes when the runs are merged in pairs.
-__device__ __forceinline__ int merge_place(const unsigned long long *run, int q, int L, int m,
-                                           unsigned long long key) {
-  const int base = q & ~(2 * L - 1), other = base + ((q & L) ? 0 : L);
-  const int len = min(L, m - other);  // of the other run, below 1 past the end
-  int below = 0;
-  for (int step = L; step > 0; step >>= 1) {
-    const int mid = below + step;
-    const bool in = mid <= len;
-    const unsigned long long o = run[in ? other + mid - 1 : q];
-    below = (in && o < key) ? mid : below;
+// Where each of K keys, key[k] at place q[k] of m keys in sorted runs of L (a
+// power of two; the last run may be short), goes when the runs are merged in
+// pairs.  With kWide the search reads three keys per round trip, which halves
+// the chain of a binary one; the K searches advance together.
+template <int K, bool kWide>
+__device__ __forceinline__ void merge_place(const unsigned long long *run, const int (&q)[K],
+                                            int L, int m, const unsigned long long (&key)[K],
+                                            int (&place)[K]) {
+  int other[K], len[K], below[K];
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    place[k] = q[k] & ~(2 * L - 1);
+    other[k] = place[k] + ((q[k] & L) ? 0 : L);
+    len[k] = min(L, m - other[k]);  // of the other run, below 1 past the end
+    below[k] = 0;
   }
-  return base + (q & (L - 1)) + below;
+  auto less = [&](int k, int mid) {  // is the run's mid-th key (from 1) below key k?
+    const bool in = mid <= len[k];
+    const unsigned long long o = run[in ? other[k] + mid - 1 : q[k]];
+    return in && o < key[k];
+  };
+  int h = L;
+  if (!kWide) {
+    for (; h > 0; h >>= 1) {
+#pragma unroll
+      for (int k = 0; k < K; ++k) below[k] += less(k, below[k] + h) ? h : 0;
+    }
+  } else if (__builtin_ctz(L) % 2 == 0) {  // an odd number of binary steps L, L/2, .., 1
+#pragma unroll
+    for (int k = 0; k < K; ++k) below[k] = less(k, L) ? L : 0;
+    h = L / 2;
+  }
+  for (h >>= 1; h > 0; h >>= 2) {
+    bool c1[K], c2[K], c3[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      c1[k] = less(k, below[k] + h);
+      c2[k] = less(k, below[k] + 2 * h);
+      c3[k] = less(k, below[k] + 3 * h);
+    }
+#pragma unroll
+    for (int k = 0; k < K; ++k) below[k] += c3[k] ? 3 * h : (c2[k] ? 2 * h : (c1[k] ? h : 0));
+  }
+#pragma unroll
+  for (int k = 0; k < K; ++k) place[k] += (q[k] & (L - 1)) + below[k];
 }
 
 // Merges m distinct keys in sorted runs of 64 in a[0, m) into one, between
-// the buffers a and b; called by all T threads of the workgroup, returns the
-// buffer that holds the result (complete for every thread).
-template <int T>
+// the buffers a and b; called by all N threads of the workgroup, returns the
+// buffer that holds the result (complete for every thread).  A thread takes
+// two keys at a time where its wave has two.  Up to 8 waves wait on the chain
+// of searches, so they search three keys wide; 16 waves keep the LDS busy, and
+// the binary search reads fewer keys.
+template <int N>
 __device__ __forceinline__ unsigned long long *merge_runs(unsigned long long *a,
                                                           unsigned long long *b, int m) {
   __syncthreads();
   for (int L = 64; L < m; L <<= 1) {
-    for (int q = threadIdx.x; q < m; q += T) {
-      const unsigned long long key = a[q];
-      b[merge_place(a, q, L, m, key)] = key;
+    for (int q0 = threadIdx.x; q0 < m; q0 += 2 * N) {
+      if (q0 - lane_id() + N < m) {
+        const int q[2] = {q0, min(q0 + N, m - 1)};
+        const unsigned long long key[2] = {a[q[0]], a[q[1]]};
+        int place[2];
+        merge_place<2, (N <= 512)>(a, q, L, m, key, place);
+        b[place[0]] = key[0];
+        b[place[1]] = key[1];  // the last key again from the lanes past it
+      } else {
+        const int q[1] = {q0};
+        const unsigned long long key[1] = {a[q0]};
+        int place[1];
+        merge_place<1, (N <= 512)>(a, q, L, m, key, place);
+        b[place[0]] = key[0];
+      }
     }
     __syncthreads();
     unsigned long long *x = a;
