@@ -28,7 +28,8 @@
 //             The last data-moving pass writes what bucket writes
 //             The second launch also checks the block table.
 //   scan      Algorithm 1's loop as prefix sums in priority order over
-//             1024-position tiles (level-2 prefix by a decoupled look-back);
+//             1024-position tiles (level-2 prefix from the earlier tiles that
+//             may grant tokens, which publish their totals);
 //             the launch's last 32 workgroups wait for every tile's hand-over,
 //             then pick the preemption victims and write the slot list and
 //             the pack / unpack move lists
@@ -74,7 +75,7 @@ constexpr int kRadix = 256;      // one workgroup's LDS sort of a small queue: 8
 constexpr int kL1 = 5;           // first-level scan values
 constexpr int kMaxScanTiles = ((1 << 20) + kScanTile - 1) / kScanTile;
 constexpr int kL2 = 7;           // second-level scan values
-constexpr int kL2Stride = 16;    // level-2 look-back words: one 128-byte line per tile
+constexpr int kL2Stride = 16;    // published level-2 words: one 128-byte line per tile
 
 // Record of one request for the priority-order scan (16 bytes).
 //   x want_blocks; for a running prefill (which never restores) the first
@@ -150,8 +151,8 @@ struct Ctl {
 };
 constexpr size_t kCtlHeaderWords = offsetof(Ctl, hist) / 4;
 
-// Sorted order with each request's scan record and block-table row offset,
-// written by the last data-moving radix pass.
+// Sorted order (the order output) and each position's scan record, written by
+// the sort.
 struct Sorted {
   unsigned *order;
   int4 *rec;
@@ -192,6 +193,20 @@ __device__ __forceinline__ T load_agent_rec(const T *src) {
   const unsigned long long *p = reinterpret_cast<const unsigned long long *>(src);
 #pragma unroll
   for (int k = 0; k < (int)(sizeof(T) / 8); ++k) w[k] = load_agent(p + k);
+  T v;
+  __builtin_memcpy(&v, w, sizeof(T));
+  return v;
+}
+
+// A whole record by 16-byte loads, for readers past an acquire fence: what the
+// fence dropped is fetched once per XCD, not once per word and workgroup.
+template <typename T>
+__device__ __forceinline__ T load_rec(const T *src) {
+  static_assert(sizeof(T) % 16 == 0, "whole 16-byte words");
+  ulonglong2 w[sizeof(T) / 16];
+  const ulonglong2 *p = reinterpret_cast<const ulonglong2 *>(src);
+#pragma unroll
+  for (int k = 0; k < (int)(sizeof(T) / 16); ++k) w[k] = p[k];
   T v;
   __builtin_memcpy(&v, w, sizeof(T));
   return v;
@@ -393,6 +408,18 @@ __device__ __forceinline__ ReqEval eval_request(const cascade_requests_t &rq,
   return r;
 }
 
+// What eval stores for request i before the scan: not admitted, nothing
+// restored.
+__device__ __forceinline__ void write_defaults(int i, const int4 &rec, const Outs &o) {
+  const bool again = rec_state(rec.w) == CASCADE_QUEUED && rec_tier(rec.w) != CASCADE_KV_HBM;
+  o.granted[i] = 0;
+  o.restore[i] = 0;
+  o.alloc_begin[i] = -1;
+  o.alloc_count[i] = 0;
+  o.action[i] = again ? CASCADE_ACT_RECOMPUTE : CASCADE_ACT_RETAIN;
+  if (o.share_leader) o.share_leader[i] = -1;
+}
+
 // How a tile-sorted step maps a request to one 64-bit key: its priority group
 // and budget over the range the parameters allow (lo, span), then its index,
 // so that all keys of a queue are distinct and below 2^63.
@@ -420,7 +447,7 @@ __global__ __launch_bounds__(NW * 64) void eval_kernel(
     size_t clear2_vec, int *info,
     Partial *__restrict__ partials, int64_t *__restrict__ budget_out,
     uint8_t *__restrict__ tier_out, unsigned long long *__restrict__ keys,
-    int4 *__restrict__ rec, KeySpec spec, unsigned long long *__restrict__ samples) {
+    int4 *__restrict__ rec, Outs o, KeySpec spec, unsigned long long *__restrict__ samples) {
   constexpr int T = NW * 64;
   static_assert(T <= 2048, "an eval workgroup's sums fit 32 bits");
   __shared__ long long s_slo[16];
@@ -474,6 +501,7 @@ __global__ __launch_bounds__(NW * 64) void eval_kernel(
     else
       keys[i] = ((unsigned long long)r.grp << 62) | r.biased;
     rec[i] = r.rec;
+    write_defaults(i, r.rec, o);
     v_held = r.held;
     v_need1 = r.need1;
     v_want1 = r.want1;
@@ -1705,7 +1733,9 @@ __device__ __forceinline__ void finish_step(const Ctl *ctl, int *info, int n, in
 struct ScanLds {
   long long scan[kWaves * kL2];
   long long red[kWaves * (kL1 + kL2 + 1)];  // earlier tiles' totals and the status flag
-  long long pre2[kL2];                      // the earlier tiles' level-2 totals (look-back)
+  long long before[2];                      // the earlier tiles' wants and needs
+  long long pre2[kL2];                      // the earlier tiles' level-2 totals
+  unsigned long long grants[(kMaxScanTiles + 63) / 64];  // bit j: tile j may grant tokens
 };
 
 // Per-request outputs of one thread's positions, stored after the hand-over.
@@ -1713,27 +1743,34 @@ struct TileOut {
   int req[kScanItems];      // request index, -1: no position
   int granted[kScanItems], restore[kScanItems], alloc_begin[kScanItems], alloc_count[kScanItems];
   int admitted_at[kScanItems];  // index in the admitted list, -1: not admitted
-  int action[kScanItems];       // -1: a running prefill (stored before the hand-over)
+  int action[kScanItems];       // -1: stored before the hand-over
   int share[kScanItems];        // share_leader output
   int p0;
 };
 
-__device__ __forceinline__ void write_tile_outputs(const TileOut &out, const Outs &o) {
+// kAll: every output of every position (a small queue).  Else only what
+// differs from what eval stored for every request, in request order, which is
+// little beyond the admitted: positions are requests in random order, and a
+// store each for all of them took 12 us at 262144 requests.
+template <bool kAll>
+__device__ __forceinline__ void write_tile_outputs(const TileOut &out, bool order,
+                                                   const Outs &o) {
 #pragma unroll
   for (int j = 0; j < kScanItems; ++j) {
     const int i = out.req[j];
     if (i < 0) continue;
-    o.order[out.p0 + j] = i;
-    o.granted[i] = out.granted[j];
-    o.restore[i] = out.restore[j];
-    o.alloc_begin[i] = out.alloc_begin[j];
-    o.alloc_count[i] = out.alloc_count[j];
+    if (order) o.order[out.p0 + j] = i;
+    if (kAll || out.admitted_at[j] >= 0) {
+      o.granted[i] = out.granted[j];
+      o.alloc_begin[i] = out.alloc_begin[j];
+      o.alloc_count[i] = out.alloc_count[j];
+    }
+    if (kAll || out.restore[j]) o.restore[i] = out.restore[j];
     if (out.action[j] >= 0) o.action[i] = (uint8_t)out.action[j];
     if (out.admitted_at[j] >= 0) o.admitted[out.admitted_at[j]] = i;
-    if (o.share_leader) o.share_leader[i] = out.share[j];
+    if (o.share_leader && (kAll || out.share[j] >= 0)) o.share_leader[i] = out.share[j];
   }
 }
-
 struct ScanConsts {
   long long bt, U, e1, cap, cap1, p_e1, g1, fh;
 };
@@ -1846,61 +1883,54 @@ __device__ __forceinline__ void scan_positions(int tile, int jn, const ScanConst
     v.l2[0] += gp ? nbj + h : 0;              // admission weight
     v.l2[1] += gp ? nbj : 0;                  // new blocks
     v.l2[2] += gp ? 1 : 0;                    // admitted count
-    v.l2[3] += gp ? 0 : h;                    // held, not granted
-    v.l2[4] += (gp || !rec_offl(w)) ? 0 : h;  // held, not granted, spill fits
+    v.l2[3] += gp ? h : 0;                    // held, granted
+    v.l2[4] += (gp && rec_offl(w)) ? h : 0;   // held, granted, spill fits
     v.l2[5] += gp ? rj : 0;                   // restored blocks
     v.l2[6] += (gp && rj > 0) ? 1 : 0;        // restoring requests
   }
 }
 
-// The earlier tiles' level-2 totals, by one wave: lane l reads tile
-// next - l, so a round trip covers 64 predecessors.  Each of the kL2 values
-// has its own flags and its own stopping point (the words of one tile are
-// published separately): a ballot finds the first unpublished and the first
-// inclusive word, and a wave sum adds the words before it.  Called by all 64
-// lanes of one wave; the sums come back in every lane.
-__device__ __forceinline__ void wave_look_back(const unsigned long long *status, int tile,
-                                               unsigned long long (&pre)[kL2], bool *timed_out) {
-  const int lane = lane_id();
-  int next[kL2];
-#pragma unroll
-  for (int k = 0; k < kL2; ++k) next[k] = tile - 1;
+// The earlier tiles' level-2 totals, by one wave: value k in lane k.  Only
+// tiles that may grant tokens (a few at the head of the order and of Tier-2,
+// as the token cap ends them) have any, so they alone publish and are read,
+// 8 tiles per round trip: lane l reads value l % 8 of the (l / 8)-th.
+__device__ __forceinline__ unsigned long long granted_before(const unsigned long long *status,
+                                                             const unsigned long long *grants,
+                                                             int tile, bool *timed_out) {
+  static_assert(kL2 <= 8, "one lane per value");
+  const int k = lane_id() & 7, slot = lane_id() >> 3;
+  unsigned long long sum = 0;
   unsigned spins = 0;
-  while (true) {
-    bool pending = false;
+  for (int b0 = 0; b0 < tile; b0 += 64) {
+    unsigned long long m = grants[b0 / 64];
+    if (tile - b0 < 64) m &= (1ull << (tile - b0)) - 1;
+    while (m) {  // uniform over the wave
+      unsigned long long mine = m;
 #pragma unroll
-    for (int k = 0; k < kL2; ++k) pending |= next[k] >= 0;
-    if (!pending) return;
-    unsigned long long w[kL2];
-#pragma unroll
-    for (int k = 0; k < kL2; ++k) {
-      const int j = next[k] - lane;
-      w[k] = j >= 0 ? load_agent(status + (size_t)j * kL2Stride + k)
-                    : (unsigned long long)kFlagInclusive;
-    }
-    bool stalled = false;
-#pragma unroll
-    for (int k = 0; k < kL2; ++k) {
-      if (next[k] < 0) continue;
-      const unsigned f = (unsigned)(w[k] & 3);
-      const uint64_t missing = __ballot(f == 0);
-      const uint64_t inclusive = __ballot(f == kFlagInclusive);
-      const int first_missing = missing ? __builtin_ctzll(missing) : 64;
-      const int first_inclusive = inclusive ? __builtin_ctzll(inclusive) : 64;
-      const bool done = first_inclusive < first_missing;
-      const int take = done ? first_inclusive + 1 : first_missing;
-      pre[k] += wave_sum(lane < take ? (w[k] >> 2) : 0ull);
-      next[k] = done ? -1 : next[k] - take;
-      stalled |= first_missing < 64 && !done;
-    }
-    if (stalled) {
-      if (++spins > kSpinLimit) {
-        *timed_out = true;
-        return;
+      for (int i = 0; i < 7; ++i) mine = i < slot ? mine & (mine - 1) : mine;
+      const bool want = mine != 0 && k < kL2;
+      const int j = want ? b0 + __builtin_ctzll(mine) : 0;
+      unsigned long long v;
+      while (true) {
+        v = want ? load_agent(status + (size_t)j * kL2Stride + k) : 1ull;
+        if (__ballot((v & 3) == 0) == 0) break;
+        if (++spins > kSpinLimit) {
+          *timed_out = true;
+          return sum;
+        }
       }
-      __builtin_amdgcn_s_sleep(1);
+      sum += v >> 2;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) m &= m - 1;  // 0 stays 0
     }
   }
+  sum += ((unsigned long long)lane_xor<8>((unsigned)(sum >> 32)) << 32) +
+         lane_xor<8>((unsigned)sum);
+  sum += ((unsigned long long)lane_xor<16>((unsigned)(sum >> 32)) << 32) +
+         lane_xor<16>((unsigned)sum);
+  sum += ((unsigned long long)lane_xor<32>((unsigned)(sum >> 32)) << 32) +
+         lane_xor<32>((unsigned)sum);
+  return sum;
 }
 
 template <bool kChained>
@@ -1931,9 +1961,8 @@ __device__ __forceinline__ long long scan_tile(int tile, int jn, const ScanConst
   const int *r = v.r, *g = v.g, *nb = v.nb, *hh = v.hh;
   const long long *y_inc = v.y_inc, *zp_inc = v.zp_inc;
 
-  // ---- level 2: the earlier tiles' totals plus this tile's.  Chained, the
-  //      tile publishes its totals and takes the earlier tiles' from a
-  //      decoupled look-back (thread k for value k); alone, they are zero.
+  // ---- level 2: the earlier tiles' totals plus this tile's; alone, the
+  //      earlier ones are zero
   block_exclusive_scan<kL2>(l2, t2, reinterpret_cast<unsigned *>(S.scan));
   long long pre2[kL2] = {0, 0, 0, 0, 0, 0, 0};
   if (kChained) {
@@ -1942,30 +1971,24 @@ __device__ __forceinline__ long long scan_tile(int tile, int jn, const ScanConst
       unsigned agg = 0;
 #pragma unroll
       for (int k = 0; k < kL2; ++k) agg = k == t ? t2[k] : agg;
-      unsigned long long *st = l2_status + (size_t)tile * kL2Stride + t;
-      if (t < kL2)
-        publish<unsigned long long>(st, agg, tile == 0 ? kFlagInclusive : kFlagAggregate);
-      unsigned long long before[kL2] = {0, 0, 0, 0, 0, 0, 0};
-      if (tile > 0) {
-        bool timed_out = false;
-        wave_look_back(l2_status, tile, before, &timed_out);
-        unsigned long long mine = 0;
-#pragma unroll
-        for (int k = 0; k < kL2; ++k) mine = k == t ? before[k] : mine;
-        if (t < kL2) publish<unsigned long long>(st, mine + agg, kFlagInclusive);
-        if (timed_out && t == 0) set_status(info, CASCADE_ETIMEOUT);
-      }
-      if (t == 0) {
-#pragma unroll
-        for (int k = 0; k < kL2; ++k) S.pre2[k] = (long long)before[k];
-      }
+      if (t < kL2 && ((S.grants[tile / 64] >> (tile % 64)) & 1))
+        publish<unsigned long long>(l2_status + (size_t)tile * kL2Stride + t, agg,
+                                    kFlagAggregate);
+      bool timed_out = false;
+      const unsigned long long before = granted_before(l2_status, S.grants, tile, &timed_out);
+      if (timed_out && t == 0) set_status(info, CASCADE_ETIMEOUT);
+      if (t < kL2) S.pre2[t] = (long long)before;
     }
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < kL2; ++k) pre2[k] = S.pre2[k];
   }
+  // X, Z: blocks held before this thread by running prefills left without a
+  // grant, all and those whose spill fits
+  const long long z0 = rec_offl(r4[0].w) ? hh[0] : 0;
   long long W = pre2[0] + l2[0], NB = pre2[1] + l2[1], AC = pre2[2] + l2[2],
-            X = pre2[3] + l2[3], Z = pre2[4] + l2[4], RR = pre2[5] + l2[5],
+            X = (y_inc[0] - hh[0]) - (pre2[3] + l2[3]),
+            Z = (zp_inc[0] - z0) - (pre2[4] + l2[4]), RR = pre2[5] + l2[5],
             RC = pre2[6] + l2[6];
 
   long long a_nb = 0, a_eh = 0, a_eoh = 0, a_n = 0, a_r = 0, a_rc = 0;
@@ -2009,9 +2032,12 @@ __device__ __forceinline__ long long scan_tile(int tile, int jn, const ScanConst
       else act = adm ? CASCADE_ACT_RESTORE : CASCADE_ACT_PREFETCH;
     }
     if (st == CASCADE_RUNNING_PREFILL) {
-      // the finishing workgroup rewrites a preempted one: store it now
-      store_agent(&o.action[i], (uint8_t)act);
+      // the finish rewrites a preempted one: stored before the hand-over (by
+      // eval when chained)
+      if (!kChained) store_agent(&o.action[i], (uint8_t)act);
       out.action[j] = -1;
+    } else if (kChained && (act == CASCADE_ACT_RETAIN || act == CASCADE_ACT_RECOMPUTE)) {
+      out.action[j] = -1;  // as eval stored it
     } else {
       out.action[j] = act;
     }
@@ -2099,7 +2125,7 @@ constexpr int kFinItems = 4;        // output entries per thread and round
 
 struct FinishKLds {
   long long red[kWaves * 8];
-  int scan_tmp[kWaves];
+  unsigned scan_tmp[kWaves * 4];
   int v_req[kFinVictims], v_held[kFinVictims], v_row0[kFinVictims], v_start[kFinVictims];
   int v_offl[kFinVictims];
   long long v_sbase[kFinVictims], v_pbase[kFinVictims];
@@ -2120,10 +2146,9 @@ __device__ __forceinline__ int fin_unpack_move_at(long long s, int nr, const Fin
 
 __device__ __forceinline__ void finish_grid(int g, int G, int n, int n_free, int n_tiles,
                                             Ctl *ctl, int *info,
-                                            const TileTot *__restrict__ tiles,
+                                            const TileTot *tiles,
                                             const int *__restrict__ free_slots,
-                                            const RpInfo *__restrict__ rp,
-                                            const RestoreEnt *__restrict__ rl,
+                                            const RpInfo *rp, const RestoreEnt *rl,
                                             const int *__restrict__ slots, const Outs &o,
                                             FinishAnyLds &U) {
   FinishKLds &L = U.par;
@@ -2135,22 +2160,24 @@ __device__ __forceinline__ void finish_grid(int g, int G, int n, int n_free, int
   // tile totals, the staged part of the restore list and the last kBlock
   // running prefills, all requested before any is used
   constexpr int kTilePer = 4, kRestPer = kRestoreCap / kBlock;
-  long long tot[7] = {0, 0, 0, 0, 0, 0, 0};
+  // the queue's totals fit 32 bits: blocks of admitted requests are at most
+  // F + H, below 2^32, and held blocks at most the block table's rows
+  unsigned tot[7] = {0, 0, 0, 0, 0, 0, 0};
   for (int j0 = 0; j0 < n_tiles; j0 += kTilePer * kBlock) {
     TileTot tt[kTilePer];
 #pragma unroll
     for (int u = 0; u < kTilePer; ++u) {
       const int j = j0 + u * kBlock + t;
-      tt[u] = j < n_tiles ? load_agent_rec(tiles + j) : TileTot{0, 0, 0, 0, 0, 0, {0, 0}};
+      tt[u] = j < n_tiles ? load_rec(tiles + j) : TileTot{0, 0, 0, 0, 0, 0, {0, 0}};
     }
 #pragma unroll
     for (int u = 0; u < kTilePer; ++u) {
-      tot[0] += tt[u].adm_nb;
-      tot[1] += tt[u].elig_h;
-      tot[2] += tt[u].elig_offl_h;
-      tot[3] += tt[u].n_adm;
-      tot[4] += tt[u].n_unpack;
-      tot[5] += tt[u].n_restore;
+      tot[0] += (unsigned)tt[u].adm_nb;
+      tot[1] += (unsigned)tt[u].elig_h;
+      tot[2] += (unsigned)tt[u].elig_offl_h;
+      tot[3] += (unsigned)tt[u].n_adm;
+      tot[4] += (unsigned)tt[u].n_unpack;
+      tot[5] += (unsigned)tt[u].n_restore;
     }
   }
   const int n_rs = min(n, kRestoreCap);
@@ -2158,22 +2185,22 @@ __device__ __forceinline__ void finish_grid(int g, int G, int n, int n_free, int
 #pragma unroll
   for (int u = 0; u < kRestPer; ++u) {
     const int j = t + u * kBlock;
-    rv[u] = j < n_rs ? load_agent_rec(rl + j) : RestoreEnt{0, 0, 0, 0};
+    rv[u] = j < n_rs ? load_rec(rl + j) : RestoreEnt{0, 0, 0, 0};
   }
   // the running-prefill list is stored from the back of the order, so its
   // last kBlock entries are requested before their count is known (a queue
   // on this path holds more than kBlock requests)
   int back = 0;
-  RpInfo ri = load_agent_rec(rp + t);
+  RpInfo ri = load_rec(rp + t);
 #pragma unroll
   for (int u = 0; u < kRestPer; ++u) {
     const int j = t + u * kBlock;
     if (j < n_rs) L.rl[j] = rv[u];
   }
   tot[6] = (t == 0 && bad_status(st)) ? 1 : 0;
-  block_sum<7>(tot, L.red);
+  block_sum<7>(tot, reinterpret_cast<unsigned *>(L.red));
   if (tot[6]) return;
-  const long long D = tot[0] - n_free, E = tot[1], EO = tot[2];
+  const long long D = (long long)tot[0] - n_free, E = tot[1], EO = tot[2];
   const long long nu = tot[4];
   const int nr = (int)tot[5];
 
@@ -2182,7 +2209,7 @@ __device__ __forceinline__ void finish_grid(int g, int G, int n, int n_free, int
   long long held_all = 0, held_offl = 0;
   while (D > 0 && back < n_rp) {
     const int e = back + t;
-    if (back != 0 && e < n_rp) ri = load_agent_rec(rp + e);
+    if (back != 0 && e < n_rp) ri = load_rec(rp + e);
     bool victim = false, kept = false;
     long long after = 0;
     if (e < n_rp && ri.eligible) {
@@ -2196,23 +2223,25 @@ __device__ __forceinline__ void finish_grid(int g, int G, int n, int n_free, int
         victim = true;
       }
     }
-    int vr[1] = {victim ? 1 : 0}, vt[1];
-    block_exclusive_scan<1>(vr, vt, L.scan_tmp);
-    const int v = nv_all + vr[0];
+    // one scan places the window's victims, their rows and whether it is the last
+    unsigned vs[4] = {victim ? 1u : 0u, victim ? (unsigned)ri.held : 0u,
+                      victim && ri.offl ? (unsigned)ri.held : 0u, kept ? 1u : 0u},
+             vt[4];
+    block_exclusive_scan<4>(vs, vt, L.scan_tmp);
+    const int v = nv_all + (int)vs[0];
     if (victim && v < kFinVictims) {
       L.v_req[v] = ri.req;
       L.v_held[v] = ri.held;
       L.v_row0[v] = ri.row0;
       L.v_offl[v] = ri.offl;
+      L.v_start[v] = (int)(held_all + vs[1]);
       L.v_sbase[v] = (long long)n_free + after;
       L.v_pbase[v] = ri.offl ? EO - (ri.pos < kstar ? ri.z : kz + ri.zp - kzp) : -1;
     }
-    long long hs[2] = {victim ? ri.held : 0, (victim && ri.offl) ? ri.held : 0};
-    block_sum<2>(hs, L.red);
-    held_all += hs[0];
-    held_offl += hs[1];
-    nv_all += vt[0];
-    if (__syncthreads_or(kept ? 1 : 0)) break;  // every earlier holder is kept too
+    held_all += vt[1];
+    held_offl += vt[2];
+    nv_all += (int)vt[0];
+    if (vt[3]) break;  // every earlier holder is kept too
     back += kBlock;
   }
   if (g == 0 && t == 0) {
@@ -2233,33 +2262,13 @@ __device__ __forceinline__ void finish_grid(int g, int G, int n, int n_free, int
     return;
   }
   const int nv = nv_all;
-  int v_total;
-  {
-    constexpr int kPer = kFinVictims / kBlock;
-    int h[kPer], run = 0;
-#pragma unroll
-    for (int u = 0; u < kPer; ++u) {
-      const int v = t * kPer + u;
-      h[u] = v < nv ? L.v_held[v] : 0;
-      run += h[u];
-    }
-    int ex[1] = {run}, tt1[1];
-    block_exclusive_scan<1>(ex, tt1, L.scan_tmp);
-    int acc = ex[0];
-#pragma unroll
-    for (int u = 0; u < kPer; ++u) {
-      const int v = t * kPer + u;
-      if (v < nv) L.v_start[v] = acc;
-      acc += h[u];
-    }
-    v_total = tt1[0];
-  }
-  if (g == 0 && t < kFinVictims) {
+  const int v_total = (int)held_all;
+  __syncthreads();
+  if (g == 0) {
     for (int v = t; v < nv; v += kBlock)
       o.action[L.v_req[v]] = (uint8_t)(L.v_offl[v] ? CASCADE_ACT_PREEMPT_OFFLOAD
                                                   : CASCADE_ACT_PREEMPT_DROP);
   }
-  __syncthreads();
 
   // this workgroup's slice of the output entries: [0, lim) free part of the
   // slot list, then v_total victim blocks, then nu restore moves
@@ -2362,59 +2371,65 @@ __device__ __forceinline__ void finish_grid(int g, int G, int n, int n_free, int
 }
 
 // Sums over tiles j < tile of the level-1 totals (l1[j*kL1 + k]), over the
-// workgroup, and the running prefills of all n_tiles tiles.  Up to 2*kBlock
-// tiles are requested at once (one round trip); an earlier launch wrote
-// them, so nothing is polled.  The step's status word rides along in the
-// same reduction: the return value says whether an earlier kernel reported
-// a failure, the same in every thread.
+// workgroup, the running prefills of all n_tiles tiles, and which tiles may
+// grant tokens at all (S.grants): the tokens needed before a tile only grow
+// along the order, so those before the caps are used up.  kBlock tiles are
+// requested at once (one round trip); an earlier launch wrote them, so
+// nothing is polled.  The step's status word rides along: the return value
+// says whether an earlier kernel reported a failure, the same in every
+// thread.  Held blocks sum to at most the block table's rows, below 2^31.
 __device__ __forceinline__ bool earlier_totals(const unsigned *__restrict__ l1,
                                                const unsigned *__restrict__ adj, int tile,
                                                int n_tiles, const int *info,
-                                               long long (&pre1)[kL1], long long &rp_total,
-                                               long long *s_red) {
-  constexpr int kPer = 2, K = kL1 + 2;
+                                               const ScanConsts &K, long long (&pre1)[kL1],
+                                               long long &rp_total, ScanLds &S) {
   const int st = load_agent(info);
-  long long v[K];
+  long long carry[2] = {0, 0};
+  unsigned v[5] = {0, 0, 0, 0, 0};  // earlier held, spill-fits, running prefills; all of them; bad
+  for (int b0 = 0; b0 < n_tiles; b0 += kBlock) {
+    // unconditional loads (tile 0 stands in past the end), masked after
+    const int j = b0 + (int)threadIdx.x, jc = j < n_tiles ? j : 0;
+    unsigned w[kL1], a0 = 0, a1 = 0;
 #pragma unroll
-  for (int k = 0; k < K; ++k) v[k] = 0;
-  for (int b0 = 0; b0 < n_tiles; b0 += kPer * kBlock) {
-    unsigned w1[kPer][kL1];
-#pragma unroll
-    for (int u = 0; u < kPer; ++u) {
-      // unconditional loads (tile 0 stands in past the end), masked after
-      const int j = b0 + u * kBlock + (int)threadIdx.x;
-      const int jc = j < n_tiles ? j : 0;
-#pragma unroll
-      for (int k = 0; k < kL1; ++k) w1[u][k] = l1[(size_t)jc * kL1 + k];
+    for (int k = 0; k < kL1; ++k) w[k] = l1[(size_t)jc * kL1 + k];
+    if (adj) {  // the followers' wants and shared tokens, taken off
+      a0 = adj[(size_t)jc * 2];
+      a1 = adj[(size_t)jc * 2 + 1];
     }
-    // shared prefixes: the followers' wants and shared tokens, taken off
-    // the earlier tiles' want and need totals
-    unsigned a1[kPer][2] = {{0, 0}, {0, 0}};
-    if (adj) {
-#pragma unroll
-      for (int u = 0; u < kPer; ++u) {
-        const int j = b0 + u * kBlock + (int)threadIdx.x;
-        const int jc = j < n_tiles ? j : 0;
-        a1[u][0] = adj[(size_t)jc * 2];
-        a1[u][1] = adj[(size_t)jc * 2 + 1];
-      }
+    const bool in = j < n_tiles;
+    long long x[2] = {in ? (long long)w[0] - a0 : 0ll, in ? (long long)w[1] - a1 : 0ll}, all[2];
+    block_exclusive_scan<2>(x, all, S.red);
+    x[0] += carry[0];
+    x[1] += carry[1];
+    carry[0] += all[0];
+    carry[1] += all[1];
+    // tokens needed before the tile, as scan_positions has them
+    const long long P = x[1] - K.bt * lmin(x[0], K.U);
+    const long long p0 = (long long)j * kScanTile;
+    const bool may =
+        in && (p0 < K.e1 ? P < K.cap1 || (p0 + kScanTile > K.e1 && K.g1 < K.cap)
+                         : K.g1 + (P - K.p_e1) < K.cap);
+    const uint64_t mask = __ballot(may);
+    if (lane_id() == 0) S.grants[b0 / 64 + wave_id()] = mask;
+    if (j == tile) {
+      S.before[0] = x[0];
+      S.before[1] = x[1];
     }
-#pragma unroll
-    for (int u = 0; u < kPer; ++u) {
-      const int j = b0 + u * kBlock + (int)threadIdx.x;
-#pragma unroll
-      for (int k = 0; k < kL1; ++k) v[k] += j < tile ? (long long)w1[u][k] : 0ll;
-      v[0] -= j < tile ? (long long)a1[u][0] : 0ll;
-      v[1] -= j < tile ? (long long)a1[u][1] : 0ll;
-      v[kL1] += j < n_tiles ? (long long)w1[u][4] : 0ll;
-    }
+    const bool earlier = j < tile;  // tile <= n_tiles - 1
+    v[0] += earlier ? w[2] : 0u;
+    v[1] += earlier ? w[3] : 0u;
+    v[2] += earlier ? w[4] : 0u;
+    v[3] += in ? w[4] : 0u;
   }
-  v[K - 1] = (threadIdx.x == 0 && bad_status(st)) ? 1 : 0;
-  block_sum<K>(v, s_red);
-#pragma unroll
-  for (int k = 0; k < kL1; ++k) pre1[k] = v[k];
-  rp_total = v[kL1];
-  return v[K - 1] != 0;
+  v[4] = (threadIdx.x == 0 && bad_status(st)) ? 1 : 0;
+  block_sum<5>(v, reinterpret_cast<unsigned *>(S.scan));  // its barrier: S.before, S.grants
+  pre1[0] = S.before[0];
+  pre1[1] = S.before[1];
+  pre1[2] = v[0];
+  pre1[3] = v[1];
+  pre1[4] = v[2];
+  rp_total = v[3];
+  return v[4] != 0;
 }
 
 // The tile's positions in priority order: request index, scan record and
@@ -2634,9 +2649,8 @@ __global__ __launch_bounds__(kBlock) void share_kernel(int n, int n_tiles, int b
 // of admitted requests, admitted count, held blocks of running prefills left
 // out (all / spill-fits), restored blocks and restoring requests.
 // A tile's level-1 prefix is the sum of the earlier tiles' totals (added by
-// the last radix pass), requested with its sorted records; its level-2
-// prefix comes from a decoupled look-back over the totals the earlier tiles
-// publish.  Workgroups past the last tile finish the step (victims, slot
+// the sort), requested with its sorted records; its level-2
+// prefix comes from the totals that the earlier tiles with grants publish.  Workgroups past the last tile finish the step (victims, slot
 // list, move lists) once every tile has handed over.
 __global__ __launch_bounds__(kBlock) void scan_kernel(
     int n, int passes, int n_tiles, Consts c, Ctl *ctl, int *info, Sorted srt,
@@ -2685,11 +2699,12 @@ __global__ __launch_bounds__(kBlock) void scan_kernel(
   load_sorted(n, srt, so, sr);
   const int nact = (int)ctl->nact;
   long long pre1[kL1], rp_total;
-  if (earlier_totals(l1_tot, share_adj, tile, n_tiles, info, pre1, rp_total, s_lds.red)) {
-    // a failed step: the look-back words say "nothing before me", so no later
+  const ScanConsts K = scan_consts(c, ctl);
+  if (earlier_totals(l1_tot, share_adj, tile, n_tiles, info, K, pre1, rp_total, s_lds)) {
+    // a failed step: this tile's words say "nothing granted", so no later
     // tile waits, and the tile is counted, so the finishing workgroups stop
     if (t < kL2) publish<unsigned long long>(l2_status + (size_t)tile * kL2Stride + t, 0ull,
-                                             kFlagInclusive);
+                                             kFlagAggregate);
     if (t == 0) atomicAdd(ctl->done + ((unsigned)tile % groups) * kTicketStride, 1u);
     return;
   }
@@ -2698,7 +2713,6 @@ __global__ __launch_bounds__(kBlock) void scan_kernel(
   int idx[kScanItems];
   int4 r4[kScanItems];
   tile_positions(n, tile, nact, srt, rec, so, sr, idx, r4, broken);
-  const ScanConsts K = scan_consts(c, ctl);
 
   TileOut out;
   const long long rp_incl =
@@ -2711,7 +2725,7 @@ __global__ __launch_bounds__(kBlock) void scan_kernel(
   wait_stores();
   __syncthreads();
   if (t == 0) atomicAdd(ctl->done + ((unsigned)tile % groups) * kTicketStride, 1u);
-  write_tile_outputs(out, o);
+  write_tile_outputs<false>(out, nact == 0, o);  // else the sort wrote the order
 }
 
 // ------------------------------------------------------------ small queues
@@ -3147,7 +3161,7 @@ __global__ __launch_bounds__(kBlock) void step_small_kernel(
   // complete before the barrier; its per-request outputs follow
   wait_stores();
   __syncthreads();
-  write_tile_outputs(out, o);
+  write_tile_outputs<true>(out, true, o);
   finish_step(ctl, info, n, c.n_free, 1, (int)n_rp, tile_tot, free_slots, rp_list, restore_list,
               slots, o, U.fin);
 }
@@ -3176,7 +3190,7 @@ __global__ __launch_bounds__(kBlock) void empty_step_kernel(int n_free, int num_
 
 struct Layout {
   size_t ctl = 0, scan1 = 0, scan2 = 0, sort_status = 0, partials = 0, keys_a = 0, keys_b = 0,
-         vals_a = 0, vals_b = 0, rec = 0, s_order = 0, s_rec = 0, rp_list = 0, restore = 0,
+         vals_a = 0, vals_b = 0, rec = 0, s_rec = 0, rp_list = 0, restore = 0,
          tile_tot = 0, share_lead = 0, share_rl = 0, share_pub = 0, share_adj = 0, total = 0;
   int sort_tiles = 0, scan_tiles = 0, eval_grid = 0;
 };
@@ -3195,7 +3209,7 @@ constexpr Layout make_layout(int32_t n) {
   // the look-back status words follow the control block: one clear covers
   // them, the sort's words last (only the launched passes' are cleared)
   L.scan1 = take((size_t)L.scan_tiles * kL1 * 4);  // level-1 totals per scan tile
-  L.scan2 = take((size_t)L.scan_tiles * kL2Stride * 8);  // level-2 look-back words per scan tile
+  L.scan2 = take((size_t)L.scan_tiles * kL2Stride * 8);  // published level-2 words per scan tile
   L.sort_status = take((size_t)kMaxPasses * L.sort_tiles * kMaxBins * 4);
   L.partials = take((size_t)L.eval_grid * sizeof(Partial));
   L.keys_a = take(np * 8);
@@ -3203,7 +3217,6 @@ constexpr Layout make_layout(int32_t n) {
   L.vals_a = take(np * 4);
   L.vals_b = take(np * 4);
   L.rec = take(np * 16);
-  L.s_order = take(np * 4);
   L.s_rec = take(np * 16);
   L.rp_list = take(np * sizeof(RpInfo));
   L.restore = take(np * sizeof(RestoreEnt));
@@ -3416,7 +3429,7 @@ int step_impl(const cascade_requests_t *rq, const cascade_block_table_t *bt,
   auto *tile_tot = reinterpret_cast<TileTot *>(ws + L.tile_tot);
   auto *sort_status = reinterpret_cast<unsigned *>(ws + L.sort_status);
   Sorted srt;
-  srt.order = reinterpret_cast<unsigned *>(ws + L.s_order);
+  srt.order = reinterpret_cast<unsigned *>(out->order);
   srt.rec = reinterpret_cast<int4 *>(ws + L.s_rec);
   auto *l1_tot = reinterpret_cast<unsigned *>(ws + L.scan1);
   auto *l2_status = reinterpret_cast<unsigned long long *>(ws + L.scan2);
@@ -3466,7 +3479,7 @@ int step_impl(const cascade_requests_t *rq, const cascade_block_table_t *bt,
                        dim3(tiles), dim3(T), 0, s, *rq, bt->row_offsets, ts->free_slots, c, n,
                        ctl, reinterpret_cast<uint4 *>(ws + clear_off), clear_vec, clear2,
                        clear2_vec, out->info, partials, out->budget_ns, out->queue_tier_out,
-                       keys_a, rec, spec, samples);
+                       keys_a, rec, o, spec, samples);
     hipLaunchKernelGGL(T <= 512 ? split_kernel<samples_of(512)> : split_kernel<samples_of(1024)>,
                        dim3(tiles * samples_of(T) / kOwnSamples), dim3(kBlock), 0, s, n,
                        ts->num_blocks, tiles, partials, bt->row_offsets, bt->slots, ctl,
@@ -3491,7 +3504,7 @@ int step_impl(const cascade_requests_t *rq, const cascade_block_table_t *bt,
     hipLaunchKernelGGL((eval_kernel<kWaves, false>), dim3(L.eval_grid), dim3(kBlock), 0, s, *rq,
                        bt->row_offsets, ts->free_slots, c, n, ctl,
                        reinterpret_cast<uint4 *>(ws + clear_off), clear_vec, clear2, clear2_vec,
-                       out->info, partials, out->budget_ns, out->queue_tier_out, keys_a, rec,
+                       out->info, partials, out->budget_ns, out->queue_tier_out, keys_a, rec, o,
                        spec, nullptr);
     // a short queue spreads prep over more workgroups (its block-table checks
     // and histograms are per workgroup); a long one keeps the global adds few

@@ -81,3 +81,16 @@ def test_bucket_beyond_lds(dev, pos):  # noqa: F811
         wait[t * T:(t + 1) * T] = rng.permutation(v)
     g, o = run_both(dev, queued(n, wait * 10 ** 9))
     assert_same(g, o, "overflow")
+
+
+@pytest.mark.parametrize("n", [1500, 9000, 70000])
+@pytest.mark.parametrize("cap,reserve", [(1, 0), (700, 65536), (5000, 32768), (60000, 4096),
+                                         (1 << 24, 8192)])
+def test_which_tiles_grant(dev, n, cap, reserve):  # noqa: F811
+    """Token caps that end in the first scan tile, in a later one, within
+    Tier-2 and never: only tiles before the caps are used up publish grants."""
+    rng = np.random.default_rng(n + cap)
+    p = helpers.base_params(token_cap=cap, tier2_reserve_q16=reserve, max_move_blocks=n // 4)
+    w = helpers.random_workload(rng, n, params=p, n_free=n // 3)
+    g, o = run_both(dev, w)
+    assert_same(g, o, f"n={n} cap={cap}")
