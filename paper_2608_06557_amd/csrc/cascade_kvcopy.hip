@@ -6,11 +6,11 @@
 // paged HBM pool, where a block's chunks are scattered over per-layer caches,
 // and a contiguous staging buffer that the host-side DMA reads or fills.
 //
-// The copy is HBM-bound: one workgroup moves one chunk per iteration with
+// The copy is HBM-bound: one workgroup moves 32 KiB per iteration with
 // 16-byte loads and stores, all loads of a thread issued before its stores so
 // that every lane keeps kUnroll requests in flight; nontemporal loads and
-// stores stream past the caches.  The grid strides over (move, layer, K/V)
-// chunks with up to kMaxGrid workgroups (about 32 per CU): measured on MI355X,
+// stores stream past the caches.  The grid strides over the blocks'
+// 32 KiB units with up to kMaxGrid workgroups (about 32 per CU): measured on MI355X,
 // a plain copy peaks near that occupancy.  The move count is read on the
 // device, so the step's output count drives the copy without a host sync.
 //
@@ -31,6 +31,7 @@ namespace {
 constexpr int kBlock = 256;
 constexpr int kUnroll = 8;
 constexpr long long kMaxGrid = 8192;
+constexpr int kWhole = 3;  // unit shape of whole chunks
 
 typedef int v4i __attribute__((ext_vector_type(4)));
 
@@ -106,20 +107,140 @@ __device__ __forceinline__ char *stage_r(char *staging, const cascade_kv_pool_t 
   return staging + ((long long)slot * 2 * pool.num_layers + r) * pool.chunk_bytes;
 }
 
-// A work item ("unit") is g consecutive chunks r0 .. r0+g-1 of one block.
-// Chunks of 32 KiB or more, or of a size that does not tile 32 KiB, are one
-// unit each and move with copy_chunk.  Smaller chunks of a multiple of 4 KiB
-// are grouped g = 32 KiB / chunk to a unit, so that each thread still has
-// kUnroll vectors in flight: vector slot u of a thread is vector
+// A work item ("unit") is a thread batch, kBlock * kUnroll vectors of 16 bytes
+// (32 KiB), of one block.  Chunks of 8 or 16 KiB tile it: a unit is then
+// g consecutive chunks r0 .. r0+g-1, and vector slot u of a thread is vector
 // ((u & (per - 1)) * kBlock + t) of chunk r0 + (u >> lg), per = 2^lg =
-// chunk / 4 KiB.
+// chunk / 4 KiB.  A chunk of 32 KiB or a multiple is a unit of its own, moved
+// by copy_chunk (1.5 % faster there than either other way).  Any other chunk size is cut as it comes: the block's chunks
+// one behind the other are one run of vectors, of which a unit is the next
+// kBlock * kUnroll, so that every thread has kUnroll vectors in flight
+// whatever the chunk (one chunk per unit left half the threads idle at 2 KiB:
+// 3.8 TB/s read and written).
 struct Units {
-  int g, lg, per_move;  // chunks per unit, log2(vectors per chunk / kBlock), units per block
+  int g, lg, per_move;  // chunks per unit (1 for runs), log2(vectors per chunk / kBlock) (-1
+                        // for runs), units per block
+  unsigned vecs;        // vectors per chunk
+  double per_vec;       // 1 / vecs
 };
 
 template <int kLg>
 __device__ __forceinline__ int unit_off(int u) {
   return ((u & ((1 << kLg) - 1)) * kBlock) + (int)threadIdx.x;
+}
+
+// v / vecs and the rest, below 2^48: the product is off by at most one.
+__device__ __forceinline__ unsigned chunk_of(long long v, const Units &un, unsigned &off) {
+  int r = (int)((double)v * un.per_vec);
+  long long rest = v - (long long)r * un.vecs;
+  if (rest < 0) --r, rest += un.vecs;
+  else if (rest >= un.vecs) ++r, rest -= un.vecs;
+  off = (unsigned)rest;
+  return (unsigned)r;
+}
+
+// Where a thread's vectors of unit k of a run lie in the pool, kBlock apart,
+// as byte offsets from the block's slot: chunk r, vector off in it.
+struct RunWalk {
+  unsigned r, off;
+  __device__ __forceinline__ RunWalk(int k, const Units &un) {
+    r = chunk_of((long long)k * (kBlock * kUnroll) + threadIdx.x, un, off);
+  }
+  __device__ __forceinline__ long long at(const cascade_kv_pool_t &pool) const {
+    return (long long)(r >> 1) * pool.layer_stride + ((r & 1) ? pool.kv_stride : 0) +
+           (long long)off * 16;
+  }
+  __device__ __forceinline__ void next(const Units &un, unsigned dr, unsigned doff) {
+    r += dr;
+    off += doff;
+    if (off >= un.vecs) {
+      off -= un.vecs;
+      ++r;
+    }
+  }
+};
+
+// Vectors of unit k of a block's run: a full batch, or what is left.
+__device__ __forceinline__ int run_count(const cascade_kv_pool_t &pool, int k, const Units &un) {
+  const long long left =
+      (long long)un.vecs * 2 * pool.num_layers - (long long)k * (kBlock * kUnroll);
+  return left < kBlock * kUnroll ? (int)left : kBlock * kUnroll;
+}
+
+__device__ __forceinline__ char *pool_slot(const cascade_kv_pool_t &pool, int slot) {
+  return static_cast<char *>(pool.base) + (long long)slot * pool.slot_stride;
+}
+
+// Unit k of a block's run, from pool slot to staging slot (or back).  Loads
+// past the block's end read its first vector instead of sitting under a
+// branch; the places are worked out again for the stores, which costs less
+// than the registers to keep them (full occupancy).
+template <bool kToStaging>
+__device__ __forceinline__ void copy_run(const cascade_kv_pool_t &pool, int slot, char *stg,
+                                         int sslot, int k, const Units &un) {
+  const int count = run_count(pool, k, un), t = (int)threadIdx.x;
+  const unsigned dr = kBlock / un.vecs, doff = kBlock - dr * un.vecs;
+  char *pb = pool_slot(pool, slot);
+  v4i *sb = reinterpret_cast<v4i *>(stage_r(stg, pool, sslot, 0)) +
+            (long long)k * (kBlock * kUnroll);
+  v4i x[kUnroll];
+  const RunWalk start(k, un);
+  RunWalk w = start;
+#pragma unroll
+  for (int u = 0; u < kUnroll; ++u) {
+    const bool in = t + u * kBlock < count;
+    x[u] = __builtin_nontemporal_load(
+        kToStaging ? reinterpret_cast<const v4i *>(pb + (in ? w.at(pool) : 0ll))
+                   : sb + (in ? t + u * kBlock : 0));
+    w.next(un, dr, doff);
+  }
+  w = start;
+#pragma unroll
+  for (int u = 0; u < kUnroll; ++u) {
+    if (t + u * kBlock < count)
+      __builtin_nontemporal_store(
+          x[u], kToStaging ? sb + t + u * kBlock : reinterpret_cast<v4i *>(pb + w.at(pool)));
+    w.next(un, dr, doff);
+  }
+}
+
+// Spill and the restore into the same unit of a run, as copy_pair: half the
+// vectors per stream at a time, the spill's stores before the restore's.
+__device__ __forceinline__ void copy_pair_run(const cascade_kv_pool_t &pool, int slot, char *spill,
+                                              int spill_slot, char *fill, int fill_slot, int k,
+                                              const Units &un) {
+  constexpr int kHalf = kUnroll / 2;
+  const int count = run_count(pool, k, un), t = (int)threadIdx.x;
+  const unsigned dr = kBlock / un.vecs, doff = kBlock - dr * un.vecs;
+  const long long v0 = (long long)k * (kBlock * kUnroll);
+  char *pb = pool_slot(pool, slot);
+  v4i *ob = reinterpret_cast<v4i *>(stage_r(spill, pool, spill_slot, 0)) + v0;
+  const v4i *ib = reinterpret_cast<const v4i *>(stage_r(fill, pool, fill_slot, 0)) + v0;
+  RunWalk w(k, un);
+#pragma unroll 1
+  for (int h = 0; h < 2; ++h) {
+    const int i0 = t + h * kHalf * kBlock;
+    const RunWalk start = w;
+    v4i a[kHalf], b[kHalf];
+#pragma unroll
+    for (int u = 0; u < kHalf; ++u) {
+      const bool in = i0 + u * kBlock < count;
+      a[u] = __builtin_nontemporal_load(
+          reinterpret_cast<const v4i *>(pb + (in ? w.at(pool) : 0ll)));
+      b[u] = __builtin_nontemporal_load(ib + (in ? i0 + u * kBlock : 0));
+      w.next(un, dr, doff);
+    }
+#pragma unroll
+    for (int u = 0; u < kHalf; ++u)
+      if (i0 + u * kBlock < count) __builtin_nontemporal_store(a[u], ob + i0 + u * kBlock);
+    w = start;
+#pragma unroll
+    for (int u = 0; u < kHalf; ++u) {
+      if (i0 + u * kBlock < count)
+        __builtin_nontemporal_store(b[u], reinterpret_cast<v4i *>(pb + w.at(pool)));
+      w.next(un, dr, doff);
+    }
+  }
 }
 
 // one unit of g = kUnroll >> kLg chunks from pool slot to staging slot (or back)
@@ -173,29 +294,34 @@ __device__ __forceinline__ void copy_pair_group(const cascade_kv_pool_t &pool, i
 }
 
 // The unit shape is a template parameter of the kernels, so each compiled
-// kernel holds one copy path: kLg < 0 whole chunks (g == 1), else a group of
-// g = kUnroll >> kLg chunks.
+// kernel holds one copy path: kLg < 0 a run of vectors, kWhole a whole chunk,
+// else a group of g = kUnroll >> kLg chunks.  `first` is the unit's number in the block's
+// run, or its first chunk.
 template <bool kToStaging, int kLg>
 __device__ __forceinline__ void copy_unit(const cascade_kv_pool_t &pool, int slot, char *stg,
-                                          int sslot, int r0, int vecs) {
-  if constexpr (kLg < 0) {
-    char *pc = pool_r(pool, slot, r0);
-    char *sc = stage_r(stg, pool, sslot, r0);
-    copy_chunk(kToStaging ? pc : sc, kToStaging ? sc : pc, vecs);
-  } else {
-    copy_group<kToStaging, kLg>(pool, slot, stg, sslot, r0);
-  }
+                                          int sslot, int first, const Units &un) {
+  if constexpr (kLg < 0)
+    copy_run<kToStaging>(pool, slot, stg, sslot, first, un);
+  else if constexpr (kLg == kWhole) {
+    char *pc = pool_r(pool, slot, first);
+    char *sc = stage_r(stg, pool, sslot, first);
+    copy_chunk(kToStaging ? pc : sc, kToStaging ? sc : pc, (int)un.vecs);
+  } else
+    copy_group<kToStaging, kLg>(pool, slot, stg, sslot, first);
 }
 
 template <int kLg>
 __device__ __forceinline__ void copy_pair_unit(const cascade_kv_pool_t &pool, int slot,
                                                char *spill, int spill_slot, char *fill,
-                                               int fill_slot, int r0, int vecs) {
+                                               int fill_slot, int first,
+                                               const Units &un) {
   if constexpr (kLg < 0)
-    copy_pair(pool_r(pool, slot, r0), stage_r(spill, pool, spill_slot, r0),
-              stage_r(fill, pool, fill_slot, r0), vecs);
+    copy_pair_run(pool, slot, spill, spill_slot, fill, fill_slot, first, un);
+  else if constexpr (kLg == kWhole)
+    copy_pair(pool_r(pool, slot, first), stage_r(spill, pool, spill_slot, first),
+              stage_r(fill, pool, fill_slot, first), (int)un.vecs);
   else
-    copy_pair_group<kLg>(pool, slot, spill, spill_slot, fill, fill_slot, r0);
+    copy_pair_group<kLg>(pool, slot, spill, spill_slot, fill, fill_slot, first);
 }
 
 __device__ __forceinline__ bool move_ok(const cascade_move_t &mv, int num_slots,
@@ -218,7 +344,6 @@ __global__ __launch_bounds__(kBlock) void kvcopy_kernel(cascade_kv_pool_t pool, 
   const int nm = min(*n_dev - first, max_moves);
   if (nm <= 0) return;
   const long long total = (long long)nm * un.per_move;
-  const int vecs = (int)(pool.chunk_bytes >> 4);
   // each item's move is requested one item ahead, as in kvmove_kernel
   cascade_move_t n_mv = {0, 0, 0, 0};
   if ((long long)blockIdx.x < total) n_mv = moves[(int)(blockIdx.x / un.per_move)];
@@ -231,7 +356,7 @@ __global__ __launch_bounds__(kBlock) void kvcopy_kernel(cascade_kv_pool_t pool, 
       flag_bad(status);
       continue;
     }
-    copy_unit<kToStaging, kLg>(pool, mv.pool_slot, staging, mv.staging_slot, r0, vecs);
+    copy_unit<kToStaging, kLg>(pool, mv.pool_slot, staging, mv.staging_slot, r0, un);
   }
 }
 
@@ -259,7 +384,6 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8, 8))) 
   const int per_move = un.per_move;
   const long long tp = (long long)np * per_move, tu = (long long)nu * per_move;
   const long long both = 2 * (tp < tu ? tp : tu), total = tp + tu;
-  const int vecs = (int)(pool.chunk_bytes >> 4);
   // the grid is even when it is below the item count, so c and
   // c ^ 1 fall in the same iteration: flipping the low bit on odd iterations
   // is a bijection that makes every workgroup alternate between pack and
@@ -317,15 +441,15 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8, 8))) 
       }
       if (ok && paired && mu.pool_slot == mv.pool_slot) {
         copy_pair_unit<kLg>(pool, mv.pool_slot, pst, mv.staging_slot, ust, mu.staging_slot, r0,
-                            vecs);
+                            un);
       } else {
-        if (ok) copy_unit<true, kLg>(pool, mv.pool_slot, pst, mv.staging_slot, r0, vecs);
-        if (paired) copy_unit<false, kLg>(pool, mu.pool_slot, ust, mu.staging_slot, r0, vecs);
+        if (ok) copy_unit<true, kLg>(pool, mv.pool_slot, pst, mv.staging_slot, r0, un);
+        if (paired) copy_unit<false, kLg>(pool, mu.pool_slot, ust, mu.staging_slot, r0, un);
       }
     } else {
       if (partner >= 0 && partner < np && phz[partner] == mi) continue;  // after its pack
       if (move_ok(mv, pool.num_slots, ust_slots))
-        copy_unit<false, kLg>(pool, mv.pool_slot, ust, mv.staging_slot, r0, vecs);
+        copy_unit<false, kLg>(pool, mv.pool_slot, ust, mv.staging_slot, r0, un);
       else
         flag_bad(status);
     }
@@ -348,18 +472,22 @@ bool list_ok(const void *staging, int32_t staging_slots, const cascade_move_t *m
 }
 
 Units units_for(const cascade_kv_pool_t *pool) {
-  Units u;
-  u.g = 1;
-  u.lg = 0;
   const long long vecs = pool->chunk_bytes >> 4;
   const int chunks = 2 * pool->num_layers;
   const int full = kBlock * kUnroll;  // vectors one thread batch covers
-  if (vecs < full && vecs % kBlock == 0 && full % vecs == 0 && chunks % (full / vecs) == 0) {
-    u.g = (int)(full / vecs);
-    while ((kBlock << u.lg) < vecs) ++u.lg;
+  if (vecs % full == 0) return {1, kWhole, chunks, (unsigned)vecs, 0.0};
+  for (int lg = 1; lg < kWhole; ++lg) {
+    const int g = kUnroll >> lg;
+    if (vecs == (kBlock << lg) && chunks % g == 0)
+      return {g, lg, chunks / g, (unsigned)vecs, 0.0};
   }
-  u.per_move = chunks / u.g;
-  return u;
+  return {1, -1, (int)((vecs * chunks + full - 1) / full), (unsigned)vecs, 1.0 / (double)vecs};
+}
+
+// One of a kernel's four unit shapes.
+template <typename Fn>
+Fn shaped(const Units &u, Fn run, Fn by4, Fn by2, Fn whole) {
+  return u.lg < 0 ? run : u.lg == 1 ? by4 : u.lg == 2 ? by2 : whole;
 }
 
 int grid_for(const Units &u, long long moves) {
@@ -377,10 +505,8 @@ int launch(const cascade_kv_pool_t *pool, const void *staging, int32_t staging_s
     return CASCADE_EINVAL;
   if (max_moves == 0) return CASCADE_OK;
   const Units u = units_for(pool);
-  auto kernel = u.g == 1 ? kvcopy_kernel<kToStaging, -1>
-                : u.lg == 0 ? kvcopy_kernel<kToStaging, 0>
-                : u.lg == 1 ? kvcopy_kernel<kToStaging, 1>
-                            : kvcopy_kernel<kToStaging, 2>;
+  auto kernel = shaped(u, kvcopy_kernel<kToStaging, -1>, kvcopy_kernel<kToStaging, 1>,
+                       kvcopy_kernel<kToStaging, 2>, kvcopy_kernel<kToStaging, kWhole>);
   hipLaunchKernelGGL(kernel, dim3(grid_for(u, max_moves)), dim3(kBlock), 0,
                      static_cast<hipStream_t>(stream), *pool, u,
                      const_cast<char *>(static_cast<const char *>(staging)), staging_slots,
@@ -431,10 +557,8 @@ extern "C" int cascade_pack_unpack(const cascade_kv_pool_t *pool, void *pack_sta
   if ((max_pack > 0 && !pack_hazard) || (max_unpack > 0 && !unpack_hazard)) return CASCADE_EINVAL;
   if (max_pack == 0 && max_unpack == 0) return CASCADE_OK;
   const Units u = units_for(pool);
-  auto kernel = u.g == 1 ? kvmove_kernel<-1>
-                : u.lg == 0 ? kvmove_kernel<0>
-                : u.lg == 1 ? kvmove_kernel<1>
-                            : kvmove_kernel<2>;
+  auto kernel =
+      shaped(u, kvmove_kernel<-1>, kvmove_kernel<1>, kvmove_kernel<2>, kvmove_kernel<kWhole>);
   hipLaunchKernelGGL(kernel, dim3(grid_for(u, (long long)max_pack + max_unpack)),
                      dim3(kBlock), 0, static_cast<hipStream_t>(stream), *pool, u,
                      static_cast<char *>(pack_staging), pack_staging_slots, pack_moves,

@@ -379,3 +379,58 @@ def test_fused_step_moves_full_size(dev, cfg):
         _check_unpacked_block(pool, geom, int(um[k]["pool_slot"]), int(um[k]["staging_slot"]), 2)
     del pool, st_in, st_out
     torch.cuda.empty_cache()
+
+
+# chunks that do not tile a 32 KiB unit: a few vectors, one short of and past
+# the 256 and 2048 vectors of a thread row and a unit, and 128 KiB
+@pytest.mark.parametrize("chunk", [32, 2048, 4080, 4112, 6144, 9216, 18432, 32752, 32784, 131072])
+@pytest.mark.parametrize("layout", ["layer_major", "block_major"])
+def test_run_units(dev, layout, chunk):
+    """Spills and restores of any chunk size, separate and fused, half of the
+    restores into spilled slots, against the oracle's memcpy order."""
+    import torch
+    from oracle import ref
+    from paper_2608_06557_amd import cascade
+    rng = np.random.default_rng(chunk)
+    nb, L, n_pack, n_unpack = 40, 3, 13, 11
+    g = _geom(layout, nb, L, chunk)
+    blk = 2 * L * chunk
+    pool_h = rng.integers(0, 256, nb * blk, dtype=np.uint8)
+    ust_h = rng.integers(0, 256, n_unpack * blk, dtype=np.uint8)
+    perm = rng.permutation(nb)
+    paired = n_unpack // 2
+    pm, um = np.zeros(n_pack, ref.MOVE_DTYPE), np.zeros(n_unpack, ref.MOVE_DTYPE)
+    pm["pool_slot"], pm["staging_slot"] = perm[:n_pack], rng.permutation(n_pack)
+    um["pool_slot"] = np.concatenate([perm[:paired], perm[n_pack:n_pack + n_unpack - paired]])
+    um["staging_slot"] = rng.permutation(n_unpack)
+    phz, uhz = np.full(n_pack, -1, np.int32), np.full(n_unpack, -1, np.int32)
+    phz[:paired] = np.arange(paired)
+    uhz[:paired] = np.arange(paired)
+    want_pool, want_pst = pool_h.copy(), np.zeros(n_pack * blk, np.uint8)
+    ref.pack(want_pool, g, want_pst, pm)
+    ref.unpack(want_pool, g, ust_h, um)
+    up = lambda a: torch.from_numpy(a.view(np.int32).copy()).cuda()
+    pm_d, um_d, phz_d, uhz_d = up(pm), up(um), up(phz), up(uhz)
+    n_dev = torch.tensor([n_pack, n_unpack], dtype=torch.int32, device="cuda")
+    ust = torch.from_numpy(ust_h).cuda()
+    for fused in (False, True):
+        pool, pst = torch.from_numpy(pool_h.copy()).cuda(), torch.zeros(n_pack * blk, dtype=torch.uint8, device="cuda")
+        st = torch.zeros(1, dtype=torch.int32, device="cuda")
+        kv, sh = dev.kv_pool_struct(pool.data_ptr(), g), dev.stream_handle()
+        pn, un = n_dev.data_ptr(), n_dev.data_ptr() + 4
+        print(layout, chunk, "fused" if fused else "separate", flush=True)
+        if fused:
+            rc = cascade.cascade_pack_unpack(kv, pst.data_ptr(), n_pack, pm_d.data_ptr(), pn,
+                                             n_pack, phz_d.data_ptr(), ust.data_ptr(), n_unpack,
+                                             um_d.data_ptr(), un, n_unpack, uhz_d.data_ptr(),
+                                             st.data_ptr(), sh)
+        else:
+            rc = cascade.cascade_pack(kv, pst.data_ptr(), n_pack, pm_d.data_ptr(), pn, n_pack,
+                                      st.data_ptr(), sh)
+            rc = rc or cascade.cascade_unpack(kv, ust.data_ptr(), n_unpack, um_d.data_ptr(), un,
+                                              n_unpack, st.data_ptr(), sh)
+        assert rc == 0
+        torch.cuda.synchronize()
+        assert int(st.item()) == 0
+        assert np.array_equal(pst.cpu().numpy(), want_pst), fused
+        assert np.array_equal(pool.cpu().numpy(), want_pool), fused
