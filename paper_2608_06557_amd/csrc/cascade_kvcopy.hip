@@ -31,7 +31,7 @@ namespace {
 constexpr int kBlock = 256;
 constexpr int kUnroll = 8;
 constexpr long long kMaxGrid = 8192;
-constexpr int kWhole = 3;  // unit shape of whole chunks
+constexpr int kWhole = -1, kRun = -2;  // unit shapes besides groups of chunks
 
 typedef int v4i __attribute__((ext_vector_type(4)));
 
@@ -107,19 +107,23 @@ __device__ __forceinline__ char *stage_r(char *staging, const cascade_kv_pool_t 
   return staging + ((long long)slot * 2 * pool.num_layers + r) * pool.chunk_bytes;
 }
 
-// A work item ("unit") is a thread batch, kBlock * kUnroll vectors of 16 bytes
-// (32 KiB), of one block.  Chunks of 8 or 16 KiB tile it: a unit is then
-// g consecutive chunks r0 .. r0+g-1, and vector slot u of a thread is vector
-// ((u & (per - 1)) * kBlock + t) of chunk r0 + (u >> lg), per = 2^lg =
-// chunk / 4 KiB.  A chunk of 32 KiB or a multiple is a unit of its own, moved
-// by copy_chunk (1.5 % faster there than either other way).  Any other chunk size is cut as it comes: the block's chunks
-// one behind the other are one run of vectors, of which a unit is the next
-// kBlock * kUnroll, so that every thread has kUnroll vectors in flight
-// whatever the chunk (one chunk per unit left half the threads idle at 2 KiB:
-// 3.8 TB/s read and written).
+// A work item ("unit") is up to a thread batch, kBlock * kUnroll vectors of 16
+// bytes (32 KiB), of one block, in the shape that its chunk size allows:
+//  - chunks of 4, 8 or 16 KiB that tile the block in batches: g consecutive
+//    chunks r0 .. r0+g-1, where vector slot u of a thread is vector
+//    ((u & (per - 1)) * kBlock + t) of chunk r0 + (u >> lg), per = 2^lg =
+//    chunk / 4 KiB;
+//  - other multiples of 4 KiB from 12 KiB on, which give every thread 3 or
+//    more vectors: one chunk, moved by copy_chunk (cut as below, 12 to 24 KiB
+//    are 1 to 5 % slower in the fused kernel);
+//  - any other size: a run.  The block's chunks one behind the other are one
+//    run of vectors and a unit is the next batch of it, so that every thread
+//    has kUnroll vectors in flight.  With a chunk a unit, 2 KiB chunks kept
+//    half the threads idle: 138 us instead of 100 for 1069 spills and 954
+//    restores of 128 KiB blocks, and 80 instead of 31 us at 1 KiB.
 struct Units {
-  int g, lg, per_move;  // chunks per unit (1 for runs), log2(vectors per chunk / kBlock) (-1
-                        // for runs), units per block
+  int g, lg, per_move;  // chunks per unit (1 but for groups), shape (groups: log2(vectors per
+                        // chunk / kBlock)), units per block
   unsigned vecs;        // vectors per chunk
   double per_vec;       // 1 / vecs
 };
@@ -294,13 +298,13 @@ __device__ __forceinline__ void copy_pair_group(const cascade_kv_pool_t &pool, i
 }
 
 // The unit shape is a template parameter of the kernels, so each compiled
-// kernel holds one copy path: kLg < 0 a run of vectors, kWhole a whole chunk,
-// else a group of g = kUnroll >> kLg chunks.  `first` is the unit's number in the block's
+// kernel holds one copy path: kRun, kWhole, else a group of g = kUnroll >> kLg
+// chunks.  `first` is the unit's number in the block's
 // run, or its first chunk.
 template <bool kToStaging, int kLg>
 __device__ __forceinline__ void copy_unit(const cascade_kv_pool_t &pool, int slot, char *stg,
                                           int sslot, int first, const Units &un) {
-  if constexpr (kLg < 0)
+  if constexpr (kLg == kRun)
     copy_run<kToStaging>(pool, slot, stg, sslot, first, un);
   else if constexpr (kLg == kWhole) {
     char *pc = pool_r(pool, slot, first);
@@ -315,7 +319,7 @@ __device__ __forceinline__ void copy_pair_unit(const cascade_kv_pool_t &pool, in
                                                char *spill, int spill_slot, char *fill,
                                                int fill_slot, int first,
                                                const Units &un) {
-  if constexpr (kLg < 0)
+  if constexpr (kLg == kRun)
     copy_pair_run(pool, slot, spill, spill_slot, fill, fill_slot, first, un);
   else if constexpr (kLg == kWhole)
     copy_pair(pool_r(pool, slot, first), stage_r(spill, pool, spill_slot, first),
@@ -335,11 +339,11 @@ __device__ __forceinline__ void flag_bad(int *status) {
 }
 
 template <bool kToStaging, int kLg>
-__global__ __launch_bounds__(kBlock) void kvcopy_kernel(cascade_kv_pool_t pool, Units un,
-                                                        char *staging, int staging_slots,
-                                                        const cascade_move_t *__restrict__ moves,
-                                                        const int *__restrict__ n_dev,
-                                                        int first, int max_moves, int *status) {
+__device__ __forceinline__ void copy_moves(const cascade_kv_pool_t &pool, const Units &un,
+                                           char *staging, int staging_slots,
+                                           const cascade_move_t *__restrict__ moves,
+                                           const int *__restrict__ n_dev, int first,
+                                           int max_moves, int *status) {
   // moves points at entry `first` of a list of *n_dev entries
   const int nm = min(*n_dev - first, max_moves);
   if (nm <= 0) return;
@@ -360,6 +364,25 @@ __global__ __launch_bounds__(kBlock) void kvcopy_kernel(cascade_kv_pool_t pool, 
   }
 }
 
+template <bool kToStaging, int kLg>
+__global__ __launch_bounds__(kBlock) void kvcopy_kernel(cascade_kv_pool_t pool, Units un,
+                                                        char *staging, int staging_slots,
+                                                        const cascade_move_t *__restrict__ moves,
+                                                        const int *__restrict__ n_dev,
+                                                        int first, int max_moves, int *status) {
+  copy_moves<kToStaging, kLg>(pool, un, staging, staging_slots, moves, n_dev, first, max_moves,
+                              status);
+}
+template <bool kToStaging>
+__global__ __launch_bounds__(kBlock) void run_copy_kernel(cascade_kv_pool_t pool, Units un,
+                                                          char *staging, int staging_slots,
+                                                          const cascade_move_t *__restrict__ moves,
+                                                          const int *__restrict__ n_dev,
+                                                          int first, int max_moves, int *status) {
+  copy_moves<kToStaging, kRun>(pool, un, staging, staging_slots, moves, n_dev, first, max_moves,
+                               status);
+}
+
 // Pack and unpack chunks interleaved: the common range holds one pack and
 // one unpack chunk per item pair, the rest belongs to the longer list.
 // Unpack move m paired with pack move j (phz[j] == m and uhz[m] == j) is
@@ -368,17 +391,12 @@ __global__ __launch_bounds__(kBlock) void kvcopy_kernel(cascade_kv_pool_t pool, 
 // overwrites them: the wait is inside the thread, none crosses workgroups.
 // The pairing test reads the same two words from both sides, so every
 // unpack move is copied exactly once.
-// Eight waves per SIMD: the prefetched move words would otherwise push the
-// scalar registers past what eight waves can hold, and at seven the copy
-// moves about 2 % fewer bytes per second (the prefetch gains about 1 % at
-// eight, measured on MI355X).
 template <int kLg>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8, 8))) void kvmove_kernel(
-    cascade_kv_pool_t pool, Units un, char *pst, int pst_slots,
-    const cascade_move_t *__restrict__ pm,
-    const int *__restrict__ pn_dev, int pmax, const int *__restrict__ phz, char *ust,
-    int ust_slots, const cascade_move_t *__restrict__ um, const int *__restrict__ un_dev,
-    int umax, const int *__restrict__ uhz, int *status) {
+__device__ __forceinline__ void move_both(
+    const cascade_kv_pool_t &pool, const Units &un, char *pst, int pst_slots,
+    const cascade_move_t *__restrict__ pm, const int *__restrict__ pn_dev, int pmax,
+    const int *__restrict__ phz, char *ust, int ust_slots, const cascade_move_t *__restrict__ um,
+    const int *__restrict__ un_dev, int umax, const int *__restrict__ uhz, int *status) {
   const int np = max(0, min(*pn_dev, pmax));
   const int nu = max(0, min(*un_dev, umax));
   const int per_move = un.per_move;
@@ -456,6 +474,29 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8, 8))) 
   }
 }
 
+// Eight waves per SIMD: the prefetched move words would otherwise push the
+// scalar registers past what eight waves can hold, and at seven the copy
+// moves about 2 % fewer bytes per second (the prefetch gains about 1 % at
+// eight, measured on MI355X).
+template <int kLg>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8, 8))) void kvmove_kernel(
+    cascade_kv_pool_t pool, Units un, char *pst, int pst_slots,
+    const cascade_move_t *__restrict__ pm, const int *__restrict__ pn_dev, int pmax,
+    const int *__restrict__ phz, char *ust, int ust_slots, const cascade_move_t *__restrict__ um,
+    const int *__restrict__ un_dev, int umax, const int *__restrict__ uhz, int *status) {
+  move_both<kLg>(pool, un, pst, pst_slots, pm, pn_dev, pmax, phz, ust, ust_slots, um, un_dev, umax,
+                 uhz, status);
+}
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8, 8))) void
+run_move_kernel(
+    cascade_kv_pool_t pool, Units un, char *pst, int pst_slots,
+    const cascade_move_t *__restrict__ pm, const int *__restrict__ pn_dev, int pmax,
+    const int *__restrict__ phz, char *ust, int ust_slots, const cascade_move_t *__restrict__ um,
+    const int *__restrict__ un_dev, int umax, const int *__restrict__ uhz, int *status) {
+  move_both<kRun>(pool, un, pst, pst_slots, pm, pn_dev, pmax, phz, ust, ust_slots, um, un_dev,
+                  umax, uhz, status);
+}
+
 bool pool_ok(const cascade_kv_pool_t *p) {
   if (!p || !p->base || p->num_layers < 1 || p->num_slots < 0) return false;
   if (p->chunk_bytes < 16 || (p->chunk_bytes & 15) || p->chunk_bytes > (1ll << 30)) return false;
@@ -475,19 +516,13 @@ Units units_for(const cascade_kv_pool_t *pool) {
   const long long vecs = pool->chunk_bytes >> 4;
   const int chunks = 2 * pool->num_layers;
   const int full = kBlock * kUnroll;  // vectors one thread batch covers
-  if (vecs % full == 0) return {1, kWhole, chunks, (unsigned)vecs, 0.0};
-  for (int lg = 1; lg < kWhole; ++lg) {
+  for (int lg = 0; lg < 3; ++lg) {
     const int g = kUnroll >> lg;
     if (vecs == (kBlock << lg) && chunks % g == 0)
       return {g, lg, chunks / g, (unsigned)vecs, 0.0};
   }
-  return {1, -1, (int)((vecs * chunks + full - 1) / full), (unsigned)vecs, 1.0 / (double)vecs};
-}
-
-// One of a kernel's four unit shapes.
-template <typename Fn>
-Fn shaped(const Units &u, Fn run, Fn by4, Fn by2, Fn whole) {
-  return u.lg < 0 ? run : u.lg == 1 ? by4 : u.lg == 2 ? by2 : whole;
+  if (vecs % kBlock == 0 && vecs >= 3 * kBlock) return {1, kWhole, chunks, (unsigned)vecs, 0.0};
+  return {1, kRun, (int)((vecs * chunks + full - 1) / full), (unsigned)vecs, 1.0 / (double)vecs};
 }
 
 int grid_for(const Units &u, long long moves) {
@@ -505,8 +540,11 @@ int launch(const cascade_kv_pool_t *pool, const void *staging, int32_t staging_s
     return CASCADE_EINVAL;
   if (max_moves == 0) return CASCADE_OK;
   const Units u = units_for(pool);
-  auto kernel = shaped(u, kvcopy_kernel<kToStaging, -1>, kvcopy_kernel<kToStaging, 1>,
-                       kvcopy_kernel<kToStaging, 2>, kvcopy_kernel<kToStaging, kWhole>);
+  auto kernel = u.lg == kRun     ? run_copy_kernel<kToStaging>
+                : u.lg == kWhole ? kvcopy_kernel<kToStaging, kWhole>
+                : u.lg == 0      ? kvcopy_kernel<kToStaging, 0>
+                : u.lg == 1      ? kvcopy_kernel<kToStaging, 1>
+                                 : kvcopy_kernel<kToStaging, 2>;
   hipLaunchKernelGGL(kernel, dim3(grid_for(u, max_moves)), dim3(kBlock), 0,
                      static_cast<hipStream_t>(stream), *pool, u,
                      const_cast<char *>(static_cast<const char *>(staging)), staging_slots,
@@ -557,8 +595,11 @@ extern "C" int cascade_pack_unpack(const cascade_kv_pool_t *pool, void *pack_sta
   if ((max_pack > 0 && !pack_hazard) || (max_unpack > 0 && !unpack_hazard)) return CASCADE_EINVAL;
   if (max_pack == 0 && max_unpack == 0) return CASCADE_OK;
   const Units u = units_for(pool);
-  auto kernel =
-      shaped(u, kvmove_kernel<-1>, kvmove_kernel<1>, kvmove_kernel<2>, kvmove_kernel<kWhole>);
+  auto kernel = u.lg == kRun     ? run_move_kernel
+                : u.lg == kWhole ? kvmove_kernel<kWhole>
+                : u.lg == 0      ? kvmove_kernel<0>
+                : u.lg == 1      ? kvmove_kernel<1>
+                                 : kvmove_kernel<2>;
   hipLaunchKernelGGL(kernel, dim3(grid_for(u, (long long)max_pack + max_unpack)),
                      dim3(kBlock), 0, static_cast<hipStream_t>(stream), *pool, u,
                      static_cast<char *>(pack_staging), pack_staging_slots, pack_moves,
