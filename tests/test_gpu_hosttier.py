@@ -144,3 +144,48 @@ def test_host_checks(dev):
     assert f(pl, **dict(args, n_moves=5)) == cascade.ENOSPC
     assert f(pl, **dict(args, events=[])) == cascade.EINVAL
     assert f(pl, **dict(args, n_moves=0, events=[])) == cascade.OK
+
+
+@pytest.mark.parametrize("how", ["pinned", "pageable", "odd_offset", "same_place", "many"])
+@pytest.mark.parametrize("chunk", [16, 4112])
+def test_link_routes(dev, how, chunk):
+    """The link kernel, and the copy commands that what it cannot take goes
+    through (pageable memory, an offset off 16 bytes, two spills to one place,
+    where the later move's block stays): the same bytes either way."""
+    import torch
+    from paper_2608_06557_amd import cascade
+    nm = 300 if how == "many" else 20       # more than one launch takes
+    rng, g, blk, mv, host_off, host_len = _case(chunk, "layer_major", chunk, nm, nb=nm + 9)
+    if how == "odd_offset":
+        host_off = host_off + 8
+        host_len += 16
+    if how == "same_place":
+        host_off[7] = host_off[3]
+    pool_h = rng.integers(0, 256, 2 * g["num_layers"] * g["num_blocks"] * chunk, dtype=np.uint8)
+    host_h = rng.integers(0, 256, host_len, dtype=np.uint8)
+    pin = (lambda t: t) if how == "pageable" else (lambda t: t.pin_memory())
+    host, back = pin(torch.from_numpy(host_h.copy())), pin(torch.zeros(host_len, dtype=torch.uint8))
+    exp_pool = pool_h.copy()
+    ref.unpack(exp_pool, g, np.concatenate([host_h[o:o + blk] for o in host_off]), mv)
+    exp_st = np.zeros(nm * blk, np.uint8)
+    ref.pack(exp_pool, g, exp_st, mv)
+    exp_back = np.zeros(host_len, np.uint8)
+    for m in range(nm):
+        exp_back[host_off[m]:host_off[m] + blk] = exp_st[m * blk:(m + 1) * blk]
+    pool = torch.from_numpy(pool_h.copy()).cuda()
+    st = torch.zeros(nm * blk, dtype=torch.uint8, device="cuda")
+    mv_d = torch.from_numpy(mv.view(np.int32).copy()).cuda()
+    n_d = torch.tensor([nm], dtype=torch.int32, device="cuda")
+    status = torch.zeros(1, dtype=torch.int32, device="cuda")
+    copy_s, comp_s = torch.cuda.Stream(), torch.cuda.current_stream()
+    _, handles = dev.event_handles(2)
+    pl = dev.kv_pool_struct(pool.data_ptr(), g)
+    for f, h in [(cascade.cascade_restore_from_host, host), (cascade.cascade_spill_to_host, back)]:
+        print(how, chunk, f.__name__, flush=True)
+        assert f(pl, st.data_ptr(), nm, h.data_ptr(), host_off, mv_d.data_ptr(), n_d.data_ptr(),
+                 nm, 150, status.data_ptr(), copy_s.cuda_stream, comp_s.cuda_stream,
+                 handles) == 0
+        torch.cuda.synchronize()
+    assert int(status.item()) == 0
+    assert np.array_equal(pool.cpu().numpy(), exp_pool)
+    assert np.array_equal(back.numpy(), exp_back)
