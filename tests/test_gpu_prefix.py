@@ -209,3 +209,40 @@ def test_null_status_and_a_single_long_request(dev):
         else:
             assert_same(g, o, "null status")
             assert int(g["n_prefix"][0]) == 16 * want
+
+
+def test_insert_contended_and_repeated(dev):
+    # many facts on few keys, in one wave and across workgroups, then the same
+    # facts again, then one more tier for keys whose slots are there
+    rng = np.random.default_rng(9)
+    hashes = rng.integers(1, 1 << 60, 500, dtype=np.uint64)
+    entries = [(int(hashes[k]), int(t)) for k, t in
+               zip(rng.integers(0, 500, 60_000) // rng.integers(1, 60, 60_000),
+                   rng.integers(0, 2, 60_000))]
+    entries += [(int(h), 0) for h in hashes]
+    reqs = [(16 * 501, [int(h) for h in hashes])] + [(64, [int(h)]) for h in hashes]
+    pw = _pw(entries, reqs)
+    d = dev.DevicePrefix(pw, capacity=1024)
+    o = ref.prefix_probe(pw["index_hashes"], pw["index_tiers"], pw["block_offsets"],
+                         pw["block_hashes"], pw["n_in"], pw["block_tokens"])
+    assert d.build() == 0
+    words = []
+    for _ in range(2):
+        assert d.probe() == 0
+        assert_same(d.fetch(), o, "contended")
+        words.append(d.index.clone())
+        import paper_2608_06557_amd.cascade as cx
+        from paper_2608_06557_amd.device import stream_handle
+        assert cx.cascade_prefix_index_insert(
+            d.index.data_ptr(), d.capacity, d.ih.data_ptr(), d.it.data_ptr(), d.n_entries,
+            d.status.data_ptr(), stream_handle(None)) == 0
+    assert torch.equal(words[0], words[1])  # facts already there change nothing
+    slots = d.index.cpu().numpy().view(np.uint64).reshape(-1, 2)
+    keys = slots[:, 0][slots[:, 0] != 0]
+    assert len(keys) == len(np.unique(keys)) == len(np.unique(hashes))
+    sets = dict(zip(slots[:, 0].tolist(), slots[:, 1].tolist()))
+    want = {}
+    for h, t in entries:
+        want[h] = want.get(h, 0) | 1 << t
+    assert all(sets[h] == w for h, w in want.items())
+    assert (slots[:, 1][slots[:, 0] == 0] == 0).all()
