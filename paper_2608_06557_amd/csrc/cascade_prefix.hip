@@ -15,8 +15,11 @@
 // stores the key; the block's deepest tier is the highest tier in its set.
 // The probe gives each request one wave, which looks up its leading blocks
 // in windows that grow while every block hits; a ballot finds the first miss
-// (a block absent, or whose set is empty), and the wave stops there.
+// (a block absent, or whose set is empty), and the wave stops there.  Very long
+// runs, and every request of a short queue, have several waves, whose windows
+// lie side by side.
 #include <hip/hip_runtime.h>
+#include <limits.h>
 #include <stdint.h>
 
 #include <algorithm>
@@ -107,24 +110,27 @@ __device__ __forceinline__ bool examine_slot(const uint4 &v, unsigned long long 
   return go && (k == h || k == 0ull);
 }
 
-// One window of a request's lookup: 64 * K leading blocks from `base`, K per
-// lane (lane l, item u: block base + 64 u + l), whose hashes h[0..K) the
+// One wave's window of a request's lookup: 64 * K leading blocks from `base`,
+// K per lane (lane l, item u: block base + 64 u + l), whose hashes h[0..K) the
 // previous window requested.  Every home slot is requested at once (and, with
-// kProbePair, the slot after it when both lie in one line), then the next
-// window's hashes, before any slot is examined; the keys past what was read
-// continue slot by slot, all together.  Every load is issued and none under a
-// branch, so that they are all in flight together: the unwanted ones read the
-// anchor, the slot that lane 0 looks up first (one line per wave, requested
-// anyway), and are ignored.  A ballot per item finds the window's first miss
-// (a block absent, or whose set is empty).  Returns true once the run has
-// ended, with matched its length; otherwise h holds the next window's hashes.
+// kProbePair, the slot after it when both lie in one line), then the hashes of
+// the wave's next window, which starts at nbase, before any slot is examined;
+// the keys past what was read continue slot by slot, all together.  Every load
+// is issued and none under a branch, so that they are all in flight together:
+// the unwanted ones read the anchor, the slot that lane 0 looks up first (one
+// line per wave, requested anyway), and are ignored.  A ballot per item finds
+// the window's first miss (a block absent, or whose set is empty), returned as
+// its position in the window (64 * K: none).  deepest takes in the deepest tier
+// before it, zero gets bit u where the lane's item u has hash 0 (reserved for
+// empty slots: a miss); h then holds the next window's hashes.
 template <int K, int KM>
-__device__ __forceinline__ bool probe_window(const uint4 *__restrict__ sl, unsigned mask,
-                                             const unsigned long long *__restrict__ hb, int lim,
-                                             int base, int lane, unsigned long long (&h)[KM],
-                                             int &matched, unsigned &deepest, bool &bad) {
+__device__ __forceinline__ int probe_window(const uint4 *__restrict__ sl, unsigned mask,
+                                            const unsigned long long *__restrict__ hb, int lim,
+                                            int base, int nbase, int lane,
+                                            unsigned long long (&h)[KM], unsigned &deepest,
+                                            unsigned &zero) {
   constexpr int KN = K < KM ? 2 * K : KM;  // items per lane of the next window
-  const int win = 64 * K, nbase = base + win;
+  constexpr int win = 64 * K;
   unsigned long long hc[K];
   bool want[K], look[K], pair[K], hit[K];
   unsigned s[K], t[K];
@@ -134,7 +140,7 @@ __device__ __forceinline__ bool probe_window(const uint4 *__restrict__ sl, unsig
     hc[u] = h[u];
     want[u] = base + u * 64 + lane < lim;
     look[u] = want[u] && hc[u] != 0ull;
-    bad = bad || (want[u] && !look[u]);  // hash 0 is reserved for empty slots: a miss
+    zero |= (want[u] && !look[u]) ? 1u << u : 0u;
     s[u] = (unsigned)fmix64(hc[u]) & mask;
   }
   const unsigned anchor = (unsigned)__builtin_amdgcn_readfirstlane((int)s[0]);
@@ -185,21 +191,117 @@ __device__ __forceinline__ bool probe_window(const uint4 *__restrict__ sl, unsig
   for (int u = 0; u < K; ++u)
     tm = (want[u] && hit[u] && u * 64 + lane < first && t[u] > tm) ? t[u] : tm;
   deepest = max(deepest, (unsigned)wave_max((unsigned long long)tm));
-  if (first < win) {
-    matched = base + first;
-    return true;
+  return first;
+}
+
+// The CSR bounds of request i: its hashes' first index and how many of them
+// count (0 with bad set when the request is invalid).  Every read of a hash
+// stays in [0, offsets[n]), the caller's array, even when another request's
+// offsets are out of order.
+__device__ __forceinline__ int request_limit(int i, int n, const int *__restrict__ offsets,
+                                             const int *__restrict__ n_in, int bt, int &b0,
+                                             bool &bad) {
+  const int b1 = offsets[i + 1], total = offsets[n], nin = n_in[i];
+  b0 = offsets[i];
+  bad = b0 < 0 || b1 < b0 || b1 > total || nin < 1 || (i == 0 && b0 != 0);
+  if (bad) b0 = 0;
+  const int have = bad ? 0 : b1 - b0, cap = bad ? 0 : (nin - 1) / bt;
+  return have < cap ? have : cap;
+}
+
+// A wave's windows start at blocks 0, 64, 192, 448, 704, ...: the end of the
+// window that block b lies in.  A hash 0 is reported when it lies before the
+// end of the window that holds the run's first miss, whichever kernel finds it.
+__device__ __forceinline__ int window_end(int b) {
+  return b < 64 ? 64 : b < 192 ? 192 : 448 + (b < 448 ? 0 : (b - 448) / 256 * 256 + 256);
+}
+
+// Lookups of one request by `nw` waves of a workgroup (`g0` the first of them),
+// from block `base` (a window's start, every earlier block cached): rounds of nw
+// adjacent windows of 64 * kProbeMaxK blocks, one per wave, until a round holds
+// a miss or the request ends.  Every wave of the workgroup calls it (lim 0: no
+// request), and a round's one barrier is also what ends the loop for all of them
+// at once.  Returns the run's length; s_round holds the answers of two rounds.
+// bad (a hash 0 that counts) is complete in the first wave, which reports it.
+struct WaveAnswer {
+  int miss, zero;  // first missing block, first hash 0 (INT_MAX: none)
+  unsigned deepest;
+  int active;      // the wave's request was not decided before this round
+};
+__device__ __forceinline__ int probe_wide(const uint4 *__restrict__ sl, unsigned mask,
+                                          const unsigned long long *__restrict__ hb, int lim,
+                                          int base, int g0, int nw,
+                                          WaveAnswer (&s_round)[2][kWaves], unsigned &deepest,
+                                          bool &bad) {
+  constexpr int K = kProbeMaxK, win = 64 * K;
+  const int lane = lane_id(), wave = wave_id();
+  unsigned long long h[K];
+  int wb = base + (wave - g0) * win, run = 0, first_zero = INT_MAX;
+#pragma unroll
+  for (int u = 0; u < K; ++u) {
+    const int j = wb + u * 64 + lane;
+    h[u] = j < lim ? hb[j] : 0ull;
   }
-  matched = nbase < lim ? nbase : lim;
-  return nbase >= lim;
+  bool active = base < lim;
+  for (int r = 0;; r ^= 1) {  // uniform over the workgroup
+    unsigned d = 0u, z = 0u;
+    int first = win, zero = INT_MAX;
+    if (active && wb < lim)  // uniform over the wave
+      first = probe_window<K, K>(sl, mask, hb, lim, wb, wb + nw * win, lane, h, d, z);
+    if (__ballot(z != 0u)) {  // invalid input
+#pragma unroll
+      for (int u = K - 1; u >= 0; --u) {
+        const uint64_t m = __ballot((z >> u) & 1u);
+        if (m) zero = wb + u * 64 + __builtin_ctzll(m);
+      }
+    }
+    if (lane == 0)
+      s_round[r][wave] = {first < win ? wb + first : INT_MAX, zero, d, (int)active};
+    __syncthreads();
+    int miss = INT_MAX, any = 0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+      const WaveAnswer a = s_round[r][w];
+      any |= a.active;
+      if (w < g0 || w >= g0 + nw) continue;
+      if (active && miss == INT_MAX) deepest = max(deepest, a.deepest);  // none past the miss
+      miss = min(miss, a.miss);
+      first_zero = min(first_zero, a.zero);
+    }
+    if (!any) return run;
+    base += nw * win;
+    wb += nw * win;
+    if (active && (miss != INT_MAX || base >= lim)) {
+      if (miss != INT_MAX) {
+        // the miss's window may reach past the round: into the hashes that the
+        // first wave holds for the next one
+        const int end = min(window_end(miss), lim);
+        bool z = first_zero < end;
+#pragma unroll
+        for (int u = 0; u < K; ++u) z = z || (wb + u * 64 + lane < end && h[u] == 0ull);
+        bad = bad || __ballot(z) != 0;
+      }
+      run = miss != INT_MAX ? miss : lim;
+      active = false;
+    }
+  }
 }
 
 // One wave per request.  Its leading blocks are looked up in windows of
 // 64 * k blocks, k doubling from 1 to kProbeMaxK while every block hits, so a
-// run of R cached blocks takes about log2 + R / (64 * kProbeMaxK) dependent
-// rounds instead of R / 64, while a short run (most of them) costs one small
-// window.  The wave stops at the first miss: blocks past it in later windows
-// cost nothing.
-__global__ __launch_bounds__(kBlock) void probe_kernel(const IndexSlot *__restrict__ slots,
+// short run (most of them) costs one small window, and the wave stops at the
+// first miss: blocks past it in later windows cost nothing.
+// From block kProbeTail on the workgroup's waves share the requests that are left
+// among them: window after window in one wave, the longest runs (5000 blocks)
+// outlast the rest of the launch.  Chat and agentic prompts, this against every
+// request alone in its wave: 16384 requests 78 against 108 us, 32768 139 against
+// 181, 65536 191 against 208.  Starting to share at block 960 measured 70, 157
+// and 184 us there, but 700 against 664 us (1984: 660) where half the prompts are
+// long ones and the chip is full without it: the waves' windows past the miss
+// then take the place of others' lookups.  72 registers (7 waves a SIMD) against
+// 76 (6): 185 against 194 us at 65536; 64 (8) spill, 215 us.
+constexpr int kProbeTail = 1984;
+__global__ __launch_bounds__(kBlock, 7) void probe_kernel(const IndexSlot *__restrict__ slots,
                                                        unsigned mask, int n,
                                                        const int *__restrict__ offsets,
                                                        const unsigned long long *__restrict__ hashes,
@@ -208,46 +310,105 @@ __global__ __launch_bounds__(kBlock) void probe_kernel(const IndexSlot *__restri
                                                        uint8_t *__restrict__ tier_out,
                                                        int *status) {
   constexpr int KM = kProbeMaxK;
-  static_assert(KM == 1 || KM == 2 || KM == 4 || KM == 8, "window sizes");
+  static_assert(KM == 4, "window_end");
   const int i = blockIdx.x * kWaves + wave_id();
-  if (i >= n) return;  // uniform over the wave
   const int lane = lane_id();
   const uint4 *sl = reinterpret_cast<const uint4 *>(slots);
-  // every read stays in [0, offsets[n]), the caller's hash array, even when
-  // another request's offsets are out of order
-  const int b0 = offsets[i], b1 = offsets[i + 1], total = offsets[n], nin = n_in[i];
-  bool bad = b0 < 0 || b1 < b0 || b1 > total || nin < 1 || (i == 0 && b0 != 0);
-  const int have = bad ? 0 : b1 - b0;
-  const int cap = bad ? 0 : (nin - 1) / bt;
-  const int lim = have < cap ? have : cap;
-  const unsigned long long *hb = hashes + (bad ? 0 : b0);
+  int b0 = 0, lim = 0;
+  bool bad = false;
+  if (i < n) lim = request_limit(i, n, offsets, n_in, bt, b0, bad);
+  const unsigned long long *hb = hashes + b0;
   int matched = 0;
-  unsigned deepest = 0;
+  unsigned deepest = 0, zero = 0;
   unsigned long long h[KM];
 #pragma unroll
   for (int u = 0; u < KM; ++u) h[u] = (u == 0 && lane < lim) ? hb[lane] : 0ull;
   int base = 0, k = 1;
   bool done = lim <= 0;
-  while (!done) {  // uniform over the wave
+  while (!done && base < kProbeTail) {  // uniform over the wave
+    const int nbase = base + 64 * k;
+    int first;
     if (k == 1)
-      done = probe_window<1, KM>(sl, mask, hb, lim, base, lane, h, matched, deepest, bad);
+      first = probe_window<1, KM>(sl, mask, hb, lim, base, nbase, lane, h, deepest, zero);
     else if (k == 2)
-      done = probe_window<(KM < 2 ? KM : 2), KM>(sl, mask, hb, lim, base, lane, h, matched,
-                                                  deepest, bad);
-    else if (k == 4)
-      done = probe_window<(KM < 4 ? KM : 4), KM>(sl, mask, hb, lim, base, lane, h, matched,
-                                                  deepest, bad);
+      first = probe_window<2, KM>(sl, mask, hb, lim, base, nbase, lane, h, deepest, zero);
     else
-      done = probe_window<KM, KM>(sl, mask, hb, lim, base, lane, h, matched, deepest, bad);
-    base += 64 * k;
+      first = probe_window<KM, KM>(sl, mask, hb, lim, base, nbase, lane, h, deepest, zero);
+    done = first < 64 * k || nbase >= lim;
+    matched = first < 64 * k ? base + first : min(nbase, lim);
+    base = nbase;
     k = k < KM ? 2 * k : KM;
   }
-  if (__ballot(bad) && lane == 0 && status) store_agent(status, (int)CASCADE_EINVAL);
+  bad = bad || __ballot(zero != 0u) != 0;
+  __shared__ int s_lim[kWaves], s_b0[kWaves];
+  __shared__ unsigned s_deep[kWaves];
+  __shared__ WaveAnswer s_round[2][kWaves];
   if (lane == 0) {
-    n_prefix_out[i] = matched * bt;
-    tier_out[i] = (uint8_t)(matched > 0 ? deepest : (unsigned)CASCADE_KV_NONE);
+    s_lim[wave_id()] = done ? 0 : lim;
+    s_b0[wave_id()] = b0;
+    s_deep[wave_id()] = deepest;
+    if (done && i < n) {
+      if (bad && status) store_agent(status, (int)CASCADE_EINVAL);
+      n_prefix_out[i] = matched * bt;
+      tier_out[i] = (uint8_t)(matched > 0 ? deepest : (unsigned)CASCADE_KV_NONE);
+    }
+  }
+  __syncthreads();
+  // m requests are left: the j-th of them takes (kWaves + m - 1 - j) / m waves
+  int m = 0, req = -1, g0 = 0, nw = 1;
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) m += s_lim[w] > 0 ? 1 : 0;
+  if (m == 0) return;  // uniform over the workgroup
+  int at = 0, j = 0;
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) {
+    if (s_lim[w] <= 0) continue;
+    const int q = (kWaves + m - 1 - j) / m;
+    if (wave_id() >= at && wave_id() < at + q) {
+      req = w;
+      g0 = at;
+      nw = q;
+    }
+    at += q;
+    ++j;
+  }
+  deepest = s_deep[req];
+  const int run = probe_wide(sl, mask, hashes + s_b0[req], s_lim[req], kProbeTail, g0, nw,
+                             s_round, deepest, bad);
+  if (lane == 0 && wave_id() == g0) {
+    const int o = blockIdx.x * kWaves + req;
+    if (bad && status) store_agent(status, (int)CASCADE_EINVAL);
+    n_prefix_out[o] = run * bt;
+    tier_out[o] = (uint8_t)deepest;
   }
 }
+
+// One workgroup per request, from its first block: every wave's window at once
+// costs lookups past the miss, but few requests leave the chip idle, and then
+// the number of dependent rounds is the time.  64 requests 14 against 25 us one
+// wave each, 1024 37 against 72, 2048 23 against 38.  Longer queues fill the chip:
+// at 8192 short prompts 27 against 17 us (long ones 52 against 48).
+__global__ __launch_bounds__(kBlock) void probe_wide_kernel(
+    const IndexSlot *__restrict__ slots, unsigned mask, int n, const int *__restrict__ offsets,
+    const unsigned long long *__restrict__ hashes, const int *__restrict__ n_in, int bt,
+    int *__restrict__ n_prefix_out, uint8_t *__restrict__ tier_out, int *status) {
+  __shared__ WaveAnswer s_round[2][kWaves];
+  const int i = blockIdx.x;
+  int b0;
+  bool bad;
+  const int lim = request_limit(i, n, offsets, n_in, bt, b0, bad);
+  unsigned deepest = 0u;
+  const int run = lim <= 0 ? 0 : probe_wide(reinterpret_cast<const uint4 *>(slots), mask,
+                                            hashes + b0, lim, 0, 0, kWaves, s_round, deepest,
+                                            bad);
+  if (threadIdx.x == 0) {
+    if (bad && status) store_agent(status, (int)CASCADE_EINVAL);
+    n_prefix_out[i] = run * bt;
+    tier_out[i] = (uint8_t)(run > 0 ? deepest : (unsigned)CASCADE_KV_NONE);
+  }
+}
+
+constexpr int kWideReqs = 2048;  // the queues that one workgroup per request pays for
 
 bool capacity_ok(int32_t capacity) {
   return capacity >= 64 && capacity <= (1 << 30) && (capacity & (capacity - 1)) == 0;
@@ -294,10 +455,18 @@ extern "C" int cascade_prefix_probe(const void *index, int32_t capacity, int32_t
   if (n == 0) return CASCADE_OK;
   if (!block_offsets || !block_hashes || !n_in || !n_prefix_out || !prefix_tier_out)
     return CASCADE_EINVAL;
-  hipLaunchKernelGGL(probe_kernel, dim3((n + kWaves - 1) / kWaves), dim3(kBlock), 0,
-                     static_cast<hipStream_t>(stream), static_cast<const IndexSlot *>(index),
-                     (unsigned)(capacity - 1), n, block_offsets,
-                     reinterpret_cast<const unsigned long long *>(block_hashes), n_in,
-                     block_tokens, n_prefix_out, prefix_tier_out, status_dev);
+  const IndexSlot *slots = static_cast<const IndexSlot *>(index);
+  const unsigned long long *hashes = reinterpret_cast<const unsigned long long *>(block_hashes);
+  const unsigned mask = (unsigned)(capacity - 1);
+  hipStream_t s = static_cast<hipStream_t>(stream);
+  if (n <= kWideReqs) {
+    hipLaunchKernelGGL(probe_wide_kernel, dim3(n), dim3(kBlock), 0, s, slots, mask, n,
+                       block_offsets, hashes, n_in, block_tokens, n_prefix_out, prefix_tier_out,
+                       status_dev);
+  } else {
+    hipLaunchKernelGGL(probe_kernel, dim3((n + kWaves - 1) / kWaves), dim3(kBlock), 0, s, slots, mask, n,
+                       block_offsets, hashes, n_in, block_tokens, n_prefix_out, prefix_tier_out,
+                       status_dev);
+  }
   return hipGetLastError() == hipSuccess ? CASCADE_OK : CASCADE_EHIP;
 }

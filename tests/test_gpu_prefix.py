@@ -211,6 +211,63 @@ def test_null_status_and_a_single_long_request(dev):
             assert int(g["n_prefix"][0]) == 16 * want
 
 
+def _edge_requests(edges, length, first_key):
+    """One request per edge m: its first miss is at block m, the last block
+    before it is in tier 1, the earlier ones in tier 0 and those past it in
+    tier 2, so a block counted past the miss would show in the tier."""
+    entries, reqs = [], []
+    for j, m in enumerate(edges):
+        seq = [first_key + j * 10_000 + b for b in range(length)]
+        entries += [(h, 0) for h in seq[:max(m - 1, 0)]]
+        if m >= 1:
+            entries.append((seq[m - 1], 1))
+        entries += [(h, 2) for h in seq[m + 1:]]
+        reqs.append((16 * length + 5, seq))
+    return entries, reqs
+
+
+@pytest.mark.parametrize("n", [32, 2048, 2049, 3001])
+def test_long_runs_shared_by_waves(dev, n):
+    # up to 2048 requests a workgroup looks up one request in rounds of 1024
+    # blocks; above, it shares the runs that reach block 1984 among its four
+    # waves, whether one, two, three or all four of its requests do (rounds of
+    # 1024, 512, 512 and 256, or 256 blocks)
+    edges = [1983, 1984, 1985, 2239, 2240, 2241, 2495, 2496, 2497, 3007, 3008, 3009,
+             4031, 4032, 0, 255, 256, 1023, 1024, 1025, 2047, 2048]
+    entries, longs = _edge_requests(edges, 4100, 1_000_000)
+    short, shorts = _edge_requests([0, 1, 40], 50, 9_000_000)
+    at = {}
+    pos = 4
+    for k, r in enumerate(longs):           # workgroups of 1, 2, 3 and 4 long runs
+        if k in (1, 3, 6):
+            pos = (pos + 7) // 4 * 4
+        at[min(pos, n - len(longs) + k)] = r
+        pos += 1
+    reqs = [at.get(i, shorts[i % 3]) for i in range(n)]
+    pw = _pw(entries + short, reqs)
+    g, o, _ = run_both(dev, pw)
+    assert_same(g, o, f"shared runs {n}")
+    assert sorted(g["n_prefix"][sorted(at)] // 16)[-1] == 4032
+
+
+@pytest.mark.parametrize("n", [1, 2500])
+@pytest.mark.parametrize("miss,zero,bad", [
+    (10, 60, True), (10, 64, False), (100, 191, True), (100, 192, False), (500, 703, True),
+    (500, 704, False), (1000, 1215, True), (1000, 1216, False), (2000, 2239, True),
+    (2000, 2240, False), (2100, 2300, False)])
+def test_zero_hash_past_the_miss(dev, n, miss, zero, bad):
+    # a hash 0 is reported when it lies in the window (0, 64, 192, 448, 704, 960,
+    # ...) that holds the first miss, or before it, however many waves look
+    entries, reqs = _edge_requests([miss], 2400, 1_000_000)
+    reqs[0][1][zero] = 0
+    reqs += [(64, [5, 6])] * (n - 1)
+    d = dev.DevicePrefix(_pw(entries, reqs))
+    assert d.build() == 0 and d.probe() == 0
+    g = d.fetch()
+    assert g["status"] == (ref.EINVAL if bad else 0)
+    assert g["n_prefix"][0] == 16 * miss and g["prefix_tier"][0] == 1
+
+
 def test_insert_contended_and_repeated(dev):
     # many facts on few keys, in one wave and across workgroups, then the same
     # facts again, then one more tier for keys whose slots are there
