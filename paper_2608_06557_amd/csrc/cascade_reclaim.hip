@@ -704,11 +704,11 @@ __device__ __forceinline__ void compact_table(const RcArgs &a, Part g) {
   }
   const int d2 = cached ? min(shift, kDigitN) : 0, s2 = shift - d2;
   const unsigned m2 = (1u << d2) - 1u;
-  // One tile per workgroup: its few candidates add to the global histogram
-  // as they are listed, so nothing is left to flush when the kernel ends;
-  // several tiles per workgroup (the deepest tier) count in LDS first.
-  const bool sub_direct = max(1, tiles_of(a.n)) <= g.count;  // uniform
-  if (d2 > 0 && !sub_direct)
+  // The candidates' digits are counted in LDS, then each digit that occurs adds
+  // once: the blocks of one iteration share a stamp, so thousands of candidates
+  // may fall on one digit, and adds to one address are served one by one
+  // (2000 of them took 20 us).
+  if (d2 > 0)
     for (int b = t; b < (1 << d2); b += kBlock) s_sub[b] = 0u;
   __syncthreads();
   for_tiles(a, g, first, [&](int tile, const Slots8 &v) {
@@ -774,12 +774,11 @@ __device__ __forceinline__ void compact_table(const RcArgs &a, Part g) {
       a.w.hash[i] = v.h[j];
       if (d2 > 0 && !sure[j]) {
         const unsigned b = (unsigned)(k[j] >> s2) & m2;
-        if (sub_direct) atomicAdd(a.w.sub + b, 1u);
-        else atomicAdd(&s_sub[b], 1u);
+        atomicAdd(&s_sub[b], 1u);
       }
     }
   });
-  if (d2 > 0 && !sub_direct) {
+  if (d2 > 0) {
     __syncthreads();
     for (int b = t; b < (1 << d2); b += kBlock) {
       const unsigned v = s_sub[b];
@@ -902,6 +901,13 @@ __device__ __forceinline__ void count_in_tile(int4 *off, unsigned e, bool below)
 //   off[t] = (reclaimed before t, demoted before t, reclaimed in t, demoted in t).
 // A threshold prefix shared by more than kStageCap candidates is resolved
 // from the whole list instead of the stage.
+// In steady use the blocks of one iteration share a stamp, so the staged
+// candidates are mostly equal: their common bits are taken off before any digit
+// pass, they are counted into the tiles' counters in LDS, and the cut tile's are
+// gathered and ranked there.  With 2000 blocks per stamp (95367 HBM, 524288 DRAM
+// slots) 39 -> 22 and 35 -> 22 us against digit passes and counters in memory,
+// and the compaction with its histogram in LDS 30 -> 12 us; with distinct stamps
+// 14 to 15 us as before.
 __global__ __launch_bounds__(kBlock) void rc_select_kernel(RcArgs a) {
   __shared__ unsigned s_hist[kRcBins];
   __shared__ int s_scan[kWaves * 2];
@@ -911,6 +917,7 @@ __global__ __launch_bounds__(kBlock) void rc_select_kernel(RcArgs a) {
   __shared__ unsigned long long s_skey[kStageLds];
   __shared__ unsigned s_sent[kStageLds];
   __shared__ int4 s_q[kTilesLds];
+  __shared__ unsigned long long s_mm[kWaves * 2];
   __shared__ int s_scan_w[kWaves * 2 * (kTilesLds / kBlock)];  // a scan of every chunk at once
   RcPlan *P = a.w.plan;
   const int t = threadIdx.x;
@@ -976,17 +983,29 @@ __global__ __launch_bounds__(kBlock) void rc_select_kernel(RcArgs a) {
     }
   }
   const bool staging = has_sub && matching <= kStageCap;
-  if (cached && !fail) {
+  const bool lds_tiles = tiles <= kTilesLds;  // every tile's counts fit in LDS
+  if (cached && !fail && (int)(blockIdx.x * kBlock) < lst.size()) {  // uniform
     const unsigned m2 = (1u << d2) - 1u;
+    // A tile's candidates lie side by side in the list, so a workgroup's share
+    // counts in LDS and each tile that occurs adds once: thousands of adds to
+    // the few lines of a small table's counters are served one by one (8 us)
+    if (lds_tiles) {
+      for (int i = t; i < tiles; i += kBlock) s_q[i] = make_int4(0, 0, 0, 0);
+      __syncthreads();
+    }
+    auto count = [&](unsigned e, bool below) {
+      if (lds_tiles) count_in_tile(s_q, e, below);
+      else count_in_tile(a.w.off, e, below);
+    };
     for_entries(ent, key, lst.size(), (int)(blockIdx.x * kBlock) + t, (int)(gridDim.x * kBlock),
                 at_list, [&](unsigned e, unsigned long long k) {
       if (!has_sub) {  // every bit of T known
-        if (k <= T) count_in_tile(a.w.off, e, k < T);
+        if (k <= T) count(e, k < T);
         return;
       }
       const unsigned dg = (unsigned)(k >> s2) & m2;
       if (dg < b2) {
-        count_in_tile(a.w.off, e, true);
+        count(e, true);
       } else if (dg == b2 && staging) {
         const unsigned p = atomicAdd(a.w.stage_n, 1u);
         if (p < (unsigned)kStageCap) {  // read by the last workgroup: agent scope
@@ -995,6 +1014,16 @@ __global__ __launch_bounds__(kBlock) void rc_select_kernel(RcArgs a) {
         }
       }
     });
+    if (lds_tiles) {
+      __syncthreads();
+      for (int i = t; i < tiles; i += kBlock) {
+        const int4 q = s_q[i];
+        unsigned long long *o = reinterpret_cast<unsigned long long *>(a.w.off + i);
+        // counts stay below 2^31: two at a time
+        if (q.x | q.y) atomicAdd(o, (unsigned)q.x | (unsigned long long)(unsigned)q.y << 32);
+        if (q.z | q.w) atomicAdd(o + 1, (unsigned)q.z | (unsigned long long)(unsigned)q.w << 32);
+      }
+    }
   }
   wait_stores();
   __syncthreads();
@@ -1008,6 +1037,17 @@ __global__ __launch_bounds__(kBlock) void rc_select_kernel(RcArgs a) {
     for (int b = t; b < kRcBins; b += kBlock) store_agent(a.w.sub + b, 0u);  // free again
   const int n_staged = (int)load_agent(a.w.stage_n);
   if (staging && n_staged != matching) fail = true;
+  // every tile's counts, in LDS when they fit: the certain ones join them, and
+  // the staged candidates are added there
+  constexpr int kChunks = kTilesLds / kBlock;
+  int4 qa[kChunks], ra[kChunks];
+#pragma unroll
+  for (int c = 0; c < kChunks; ++c) {  // every chunk's records requested at once
+    const int tile = c * kBlock + t;
+    const bool on = lds_tiles && tile < tiles;
+    qa[c] = on ? load_counts(a.w.off, tile) : make_int4(0, 0, 0, 0);
+    ra[c] = on ? a.w.rec[tile] : make_int4(0, 0, 0, 0);
+  }
   // the candidates on T's first digits: the stage (in LDS when it fits),
   // or the whole list filtered by those digits
   const unsigned long long *skey = a.w.stage_key;
@@ -1023,8 +1063,19 @@ __global__ __launch_bounds__(kBlock) void rc_select_kernel(RcArgs a) {
         s_sent[i] = load_agent(sent + i);
       }
     }
-    __syncthreads();
   }
+#pragma unroll
+  for (int c = 0; c < kChunks; ++c) {
+    const int tile = c * kBlock + t;
+    if (lds_tiles && tile < tiles) {
+      int4 q = qa[c];
+      q.x += ra[c].y;  // certainly reclaimed: below T
+      q.z += ra[c].w;
+      if (!cached) q.y += ra[c].z;  // empty slots only: every candidate is key 0 = T, none demoted
+      s_q[tile] = q;
+    }
+  }
+  __syncthreads();
   auto at_stage = [](int fi) { return fi; };
   auto for_matching = [&](auto &&f) {
     if (in_lds) {
@@ -1067,6 +1118,32 @@ __global__ __launch_bounds__(kBlock) void rc_select_kernel(RcArgs a) {
     }
     __syncthreads();
   }
+  //    (blocks of one iteration share a stamp: often all of them are equal)
+  if (!fail && has_sub && shift > 0 && in_lds && n_staged > 0) {
+    unsigned long long mn = ~0ull, mx = 0ull;
+    for (int i = t; i < n_staged; i += kBlock) {
+      mn = min(mn, s_skey[i]);
+      mx = max(mx, s_skey[i]);
+    }
+    mn = wave_min(mn);
+    mx = wave_max(mx);
+    if (lane_id() == 0) {
+      s_mm[wave_id() * 2] = mn;
+      s_mm[wave_id() * 2 + 1] = mx;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+      mn = min(mn, s_mm[w * 2]);
+      mx = max(mx, s_mm[w * 2 + 1]);
+    }
+    // the bits above the highest that differs are every staged key's
+    const int differ = bit_width64(mn ^ mx);
+    if (differ < shift) {
+      shift = differ;
+      T = differ ? mn >> differ << differ : mn;
+    }
+  }
   while (!fail && has_sub && shift > 0) {
     const int d = min(shift, kDigitN), s = shift - d;
     const unsigned m = (1u << d) - 1u;
@@ -1091,85 +1168,72 @@ __global__ __launch_bounds__(kBlock) void rc_select_kernel(RcArgs a) {
   }
   // 2. the candidates on T's first digits, counted against T
   if (!fail && has_sub) {
-    for_matching([&](unsigned e, unsigned long long k) {
-      if (k <= T) count_in_tile(a.w.off, e, k < T);
-    });
-    wait_stores();
+    if (lds_tiles) {
+      for_matching([&](unsigned e, unsigned long long k) {
+        if (k <= T) count_in_tile(s_q, e, k < T);
+      });
+    } else {
+      for_matching([&](unsigned e, unsigned long long k) {
+        if (k <= T) count_in_tile(a.w.off, e, k < T);
+      });
+      wait_stores();
+    }
   }
   __syncthreads();
-  acquire_agent();  // the counters are read back from memory
+  if (!lds_tiles) acquire_agent();  // the counters are read back from memory
 
   // 3. per tile: the certain ones join the counts; the tile holding the
   //    take-th key T in slot order
   const int take = rank + 1;
   int carry = 0;
   if (t == 0) s_found[0] = -1;
-  // one chunk of kBlock tiles, in tile order (called by every thread)
-  auto tile_chunk = [&](int tile, int4 q, const int4 &r) {
-    if (tile < tiles) {
-      q.x += r.y;  // certainly reclaimed: below T
-      q.z += r.w;
-      if (!cached) q.y += r.z;  // empty slots only: every candidate is key 0 = T, none demoted
-      if (tiles <= kTilesLds) s_q[tile] = q;
-      else a.w.off[tile] = q;
-    } else {
-      q = make_int4(0, 0, 0, 0);
-    }
-    int ex[1] = {q.y}, tot[1];
+  if (tiles <= kBlock) {
+    int ex[1] = {t < tiles ? s_q[t].y : 0}, tot[1];
+    const int y = ex[0];
     block_exclusive_scan<1, int>(ex, tot, s_scan);
-    if (take > carry + ex[0] && take <= carry + ex[0] + q.y) {
-      s_found[0] = tile;
-      s_found[1] = take - carry - ex[0];  // keys T taken in that tile
+    if (take > ex[0] && take <= ex[0] + y) {
+      s_found[0] = t;
+      s_found[1] = take - ex[0];  // keys T taken in that tile
     }
-    carry += tot[0];
-  };
-  if (tiles <= kTilesLds) {
-    // every chunk's records requested at once
-    constexpr int kChunks = kTilesLds / kBlock;
-    int4 qa[kChunks], ra[kChunks];
+  } else if (lds_tiles) {
+    // every chunk's keys T counted in one block scan (chunk c holds tiles
+    // c * kBlock + thread), then chunk by chunk the tile holding the take-th
+    int ys[kChunks], y[kChunks], tot[kChunks];
 #pragma unroll
     for (int c = 0; c < kChunks; ++c) {
       const int tile = c * kBlock + t;
-      qa[c] = tile < tiles ? load_counts(a.w.off, tile) : make_int4(0, 0, 0, 0);
-      ra[c] = tile < tiles ? a.w.rec[tile] : make_int4(0, 0, 0, 0);
+      ys[c] = y[c] = tile < tiles ? s_q[tile].y : 0;
     }
-    if (tiles <= kBlock) {
-      tile_chunk(t, qa[0], ra[0]);
-    } else {
-      // every chunk's keys T counted in one block scan (chunk c holds tiles
-      // c * kBlock + thread), then chunk by chunk the tile holding the take-th
-      int ys[kChunks], tot[kChunks];
+    block_exclusive_scan<kChunks, int>(ys, tot, s_scan_w);
+    int base = 0;
 #pragma unroll
-      for (int c = 0; c < kChunks; ++c) {
-        const int tile = c * kBlock + t;
-        int4 q = make_int4(0, 0, 0, 0);
-        if (tile < tiles) {
-          q = qa[c];
-          q.x += ra[c].y;  // certainly reclaimed: below T
-          q.z += ra[c].w;
-          if (!cached) q.y += ra[c].z;  // empty slots only: every candidate is key 0 = T
-          s_q[tile] = q;
-        }
-        qa[c] = q;
-        ys[c] = q.y;
+    for (int c = 0; c < kChunks; ++c) {
+      const int pre = base + ys[c];
+      if (take > pre && take <= pre + y[c]) {
+        s_found[0] = c * kBlock + t;
+        s_found[1] = take - pre;  // keys T taken in that tile
       }
-      block_exclusive_scan<kChunks, int>(ys, tot, s_scan_w);
-      int base = 0;
-#pragma unroll
-      for (int c = 0; c < kChunks; ++c) {
-        const int pre = base + ys[c], y = qa[c].y;
-        if (take > pre && take <= pre + y) {
-          s_found[0] = c * kBlock + t;
-          s_found[1] = take - pre;  // keys T taken in that tile
-        }
-        base += tot[c];
-      }
+      base += tot[c];
     }
   } else {
-    for (int c0 = 0; c0 < tiles; c0 += kBlock) {
+    for (int c0 = 0; c0 < tiles; c0 += kBlock) {  // in tile order
       const int tile = c0 + t;
-      const int4 r = tile < tiles ? a.w.rec[tile] : make_int4(0, 0, 0, 0);
-      tile_chunk(tile, tile < tiles ? load_counts(a.w.off, tile) : make_int4(0, 0, 0, 0), r);
+      int4 q = make_int4(0, 0, 0, 0);
+      if (tile < tiles) {
+        const int4 r = a.w.rec[tile];
+        q = load_counts(a.w.off, tile);
+        q.x += r.y;  // as above
+        q.z += r.w;
+        if (!cached) q.y += r.z;
+        a.w.off[tile] = q;
+      }
+      int ex[1] = {q.y}, tot[1];
+      block_exclusive_scan<1, int>(ex, tot, s_scan);
+      if (take > carry + ex[0] && take <= carry + ex[0] + q.y) {
+        s_found[0] = tile;
+        s_found[1] = take - carry - ex[0];
+      }
+      carry += tot[0];
     }
   }
   __syncthreads();
@@ -1182,26 +1246,34 @@ __global__ __launch_bounds__(kBlock) void rc_select_kernel(RcArgs a) {
   __syncthreads();
   if (t == 0) s_found[2] = -1;
   __syncthreads();
-  if (!fail && cut >= 0 && in_lds && n_staged <= kTieLds) {
-    // every candidate equal to T is staged: rank the cut tile's by slot
-    if (t == 0) s_found[1] = 0;
+  bool ranked = false;
+  if (!fail && cut >= 0 && in_lds) {
+    // every candidate equal to T is staged: the cut tile's, ranked by slot
+    if (t == 0) s_found[0] = s_found[1] = 0;
     __syncthreads();
     for (int i = t; i < n_staged; i += kBlock) {
-      const int slot = (int)(s_sent[i] & kEntSlot);
-      if (s_skey[i] != T || slot / kRcTile != cut) continue;
-      int before = 0;
-      for (int j = 0; j < n_staged; ++j) {
-        const int sj = (int)(s_sent[j] & kEntSlot);
-        before += (s_skey[j] == T && sj / kRcTile == cut && sj < slot) ? 1 : 0;
-      }
-      if (before < r_cut && (s_sent[i] & kEntDem)) atomicAdd(&s_found[1], 1);
-      if (before == r_cut - 1) s_found[2] = slot;
+      const unsigned e = s_sent[i];
+      if (s_skey[i] == T && (int)(e & kEntSlot) / kRcTile == cut)
+        s_hist[atomicAdd(&s_found[0], 1)] = e;
     }
     __syncthreads();
-    tie_slot = s_found[2];
-    dem_cut = s_found[1];
-    if (tie_slot < 0) fail = true;
-  } else if (!fail && cut >= 0) {
+    const int m = s_found[0];
+    ranked = m <= kBlock;
+    if (ranked) {
+      if (t < m) {
+        const unsigned e = s_hist[t];
+        int before = 0;
+        for (int j = 0; j < m; ++j) before += (s_hist[j] & kEntSlot) < (e & kEntSlot) ? 1 : 0;
+        if (before < r_cut && (e & kEntDem)) atomicAdd(&s_found[1], 1);
+        if (before == r_cut - 1) s_found[2] = (int)(e & kEntSlot);
+      }
+      __syncthreads();
+      tie_slot = s_found[2];
+      dem_cut = s_found[1];
+      if (tie_slot < 0) fail = true;
+    }
+  }
+  if (!fail && cut >= 0 && !ranked) {
     if (t < 64) {
       const int4 r = a.w.rec[cut];
       const int end = r.x + r.y + r.z;

@@ -404,3 +404,22 @@ def test_lookup_after_reclaim_reads_the_new_tiers(dev):
     assert np.array_equal(r["prefix_tier"], o["prefix_tier"])
     # some blocks became misses: dropped from NVMe with no copy left
     assert (masks == 0).any()
+
+
+@pytest.mark.parametrize("group", [1, 40, 255, 256, 257, 1978, 2049, 5000])
+def test_blocks_of_one_iteration_share_a_stamp(dev, group):
+    # every `group` blocks share a stamp and the stamps lie 20 ms apart, so the
+    # threshold's digits hold whole groups and the cut falls inside one, or on
+    # its edge; a few odd stamps sit between them
+    rng = np.random.default_rng(group)
+    sizes = (30_000, 70_001, 150_003)
+    for need in (2 * group if group > 1 else 777, 2 * group + group // 2 + 1):
+        w = synth.make_tier_workload(2, seed=group, sizes=sizes, needs=(need, 300, 5))
+        for t, tb in enumerate(w["tables"]):
+            n = sizes[t]
+            age = rng.permutation(n) // group
+            tb["last_use_ns"][:] = 1_700_000_000_000_000_000 - age * 20_000_000
+            odd = rng.integers(0, n, 50)
+            tb["last_use_ns"][odd] -= rng.integers(0, 10_000_000, 50)
+        g, rc, outs, masks, _ = run_both(dev, w)
+        assert_chain_same(w, g, rc, outs, masks, f"group {group} need {need}")
