@@ -3193,7 +3193,17 @@ struct Layout {
          vals_a = 0, vals_b = 0, rec = 0, s_rec = 0, rp_list = 0, restore = 0,
          tile_tot = 0, share_lead = 0, share_rl = 0, share_pub = 0, share_adj = 0, total = 0;
   int sort_tiles = 0, scan_tiles = 0, eval_grid = 0;
+  // the tiled sort (up to kTiledMax requests): its tiles, and its samples and
+  // splitters in the radix passes' status words, which it does not use
+  int tile = 0, tiles = 0;
+  size_t samples = 0, splitters = 0, tiled_end = 0;
 };
+// All of them fit there: at most two tiles per 512-key sort tile, each with at
+// most samples_of(1024) samples and one splitter.  What lies behind them
+// (eval's partials) is read while splitters are stored.
+static_assert(2 * (samples_of(1024) + 1) * 8 <= kMaxPasses * kMaxBins * 4 &&
+                  kSortTileTiny == 2 * 256,
+              "the tiled sort's words stay in the status words");
 
 constexpr size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
 
@@ -3211,6 +3221,13 @@ constexpr Layout make_layout(int32_t n) {
   L.scan1 = take((size_t)L.scan_tiles * kL1 * 4);  // level-1 totals per scan tile
   L.scan2 = take((size_t)L.scan_tiles * kL2Stride * 8);  // published level-2 words per scan tile
   L.sort_status = take((size_t)kMaxPasses * L.sort_tiles * kMaxBins * 4);
+  if (n > 0 && n <= kTiledMax) {
+    L.tile = n <= kTiledTiles * 256 ? 256 : (n <= kTiledTiles * 512 ? 512 : 1024);
+    L.tiles = (n + L.tile - 1) / L.tile;
+    L.samples = L.sort_status;
+    L.splitters = L.samples + (size_t)L.tiles * samples_of(L.tile) * 8;
+    L.tiled_end = L.splitters + (size_t)L.tiles * 8;
+  }
   L.partials = take((size_t)L.eval_grid * sizeof(Partial));
   L.keys_a = take(np * 8);
   L.keys_b = take(np * 8);
@@ -3465,11 +3482,9 @@ int step_impl(const cascade_requests_t *rq, const cascade_block_table_t *bt,
     // It clears only the level-1 totals and the scan's words.
     spec.lo = (unsigned long long)(range.lo + ((__int128)1 << 61));
     spec.span = (unsigned long long)range.span;
-    const int T = n <= kTiledTiles * 256 ? 256 : (n <= kTiledTiles * 512 ? 512 : 1024);
-    const int tiles = (n + T - 1) / T;
-    // samples and splitters use the radix passes' status words
-    auto *samples = reinterpret_cast<unsigned long long *>(ws + L.sort_status);
-    auto *splitters = samples + kTiledTiles * samples_of(1024);
+    const int T = L.tile, tiles = L.tiles;
+    auto *samples = reinterpret_cast<unsigned long long *>(ws + L.samples);
+    auto *splitters = reinterpret_cast<unsigned long long *>(ws + L.splitters);
     const size_t clear_off = L.ctl + offsetof(Ctl, done);
     const size_t clear_vec = (L.sort_status - clear_off) / 16;
     static_assert(offsetof(Ctl, done) % 16 == 0, "16-byte clears");

@@ -31,9 +31,10 @@ def queued(n, elapsed, slo_s=600):
     return w
 
 
-# 256-, 512- and 1024-request tiles, full and short, and the radix sort above
-@pytest.mark.parametrize("n", [1025, 1279, 1281, 65536, 65537, 65281, 131072, 131073, 131585,
-                               262143, 262144, 262145])
+# 256-, 512- and 1024-request tiles, full and short, and the radix sort above;
+# 1025 to 2048 requests are where the samples and splitters have the least room
+@pytest.mark.parametrize("n", [1025, 1279, 1281, 1536, 1537, 1792, 1793, 2047, 2048, 65536,
+                               65537, 65281, 131072, 131073, 131585, 262143, 262144, 262145])
 def test_tile_size_edges(dev, n):  # noqa: F811
     import paper_2608_06557_amd.synth as synth
     w = synth.make_workload(3 if n < 100000 else 4, seed=n, n=n)
