@@ -149,12 +149,12 @@ def test_host_checks(dev):
 @pytest.mark.parametrize("how", ["pinned", "pageable", "odd_offset", "same_place", "many"])
 @pytest.mark.parametrize("chunk", [16, 4112])
 def test_link_routes(dev, how, chunk):
-    """The link kernel, and the copy commands that what it cannot take goes
-    through (pageable memory, an offset off 16 bytes, two spills to one place,
-    where the later move's block stays): the same bytes either way."""
+    """Pinned and pageable host memory, offsets off 16 bytes, two spills to one
+    place (the later move's block stays) and more moves than a batch: the same
+    bytes whatever route the host link's copies take."""
     import torch
     from paper_2608_06557_amd import cascade
-    nm = 300 if how == "many" else 20       # more than one launch takes
+    nm = 300 if how == "many" else 20
     rng, g, blk, mv, host_off, host_len = _case(chunk, "layer_major", chunk, nm, nb=nm + 9)
     if how == "odd_offset":
         host_off = host_off + 8
@@ -189,3 +189,75 @@ def test_link_routes(dev, how, chunk):
     assert int(status.item()) == 0
     assert np.array_equal(pool.cpu().numpy(), exp_pool)
     assert np.array_equal(back.numpy(), exp_back)
+
+
+@pytest.mark.parametrize("way", ["spill", "restore"])
+def test_the_link_leaves_the_gpu_to_others(dev, way):
+    """Kernels of another stream run at their usual pace while the host link
+    moves blocks: each launch boundary on the GPU waits for the requests in
+    flight before it, so a copy over the link that keeps many of them in
+    flight from the compute units slows every other stream (a step 28 times).
+    The bound of 4 leaves room for the copies' own share of HBM and for a
+    cold clock; the copy engines measure 1.0 to 1.3."""
+    import torch
+    import paper_2608_06557_amd.synth as synth
+    from paper_2608_06557_amd import cascade
+    nm, chunk, layers = 160, 32768, 32
+    g = _geom("layer_major", nm, layers, chunk)
+    blk = 2 * layers * chunk
+    mv = np.zeros(nm, ref.MOVE_DTYPE)
+    mv["pool_slot"], mv["staging_slot"] = np.arange(nm), np.arange(nm)
+    host_off = np.random.default_rng(4).permutation(nm).astype(np.int64) * blk
+    pool = torch.zeros(nm * blk, dtype=torch.uint8, device="cuda")
+    st = torch.zeros(nm * blk, dtype=torch.uint8, device="cuda")
+    host = torch.zeros(nm * blk, dtype=torch.uint8, pin_memory=True)
+    mv_d = torch.from_numpy(mv.view(np.int32).copy()).cuda()
+    n_d = torch.tensor([nm], dtype=torch.int32, device="cuda")
+    status = torch.zeros(1, dtype=torch.int32, device="cuda")
+    pl = dev.kv_pool_struct(pool.data_ptr(), g)
+    f = cascade.cascade_spill_to_host if way == "spill" else cascade.cascade_restore_from_host
+    copy_s, comp_s = torch.cuda.Stream(), torch.cuda.current_stream()
+    # streams share a few hardware queues: one of these has a queue that waits
+    # for neither of the call's streams
+    sides = [torch.cuda.Stream() for _ in range(4)]
+    _, handles = dev.event_handles(2)
+    d = dev.DeviceStep(synth.make_workload(1, seed=2, n=8192))
+    stamp = lambda: torch.cuda.Event(enable_timing=True)
+    runs = 150
+
+    def steps(side):
+        with torch.cuda.stream(side):
+            at = [stamp() for _ in range(runs + 1)]
+            at[0].record()
+            for e in at[1:]:
+                assert d.run() == 0
+                e.record()
+        return at
+
+    def link():
+        assert f(pl, st.data_ptr(), nm, host.data_ptr(), host_off, mv_d.data_ptr(),
+                 n_d.data_ptr(), nm, 16, status.data_ptr(), copy_s.cuda_stream,
+                 comp_s.cuda_stream, handles) == 0
+
+    link()
+    steps(sides[0])
+    torch.cuda.synchronize()                 # both paths are warm
+    t = steps(sides[0])
+    torch.cuda.synchronize()
+    alone = sorted(a.elapsed_time(b) for a, b in zip(t, t[1:]))[runs // 2]
+    best = []
+    for side in sides:
+        begin, end = stamp(), stamp()
+        begin.record(comp_s)
+        link()
+        end.record(copy_s)
+        t = steps(side)
+        torch.cuda.synchronize()
+        link_ms = begin.elapsed_time(end)
+        beside = [a.elapsed_time(b) for a, b in zip(t, t[1:])
+                  if begin.elapsed_time(a) < link_ms]
+        print(f"{way}: link {link_ms:.2f} ms, {len(beside)} steps beside it, alone "
+              f"{alone:.4f} ms", flush=True)
+        best = max(best, beside, key=len)
+    assert len(best) >= 4
+    assert sorted(best)[len(best) // 2] < 4 * alone
