@@ -120,7 +120,10 @@ __device__ __forceinline__ char *stage_r(char *staging, const cascade_kv_pool_t 
 //    run of vectors and a unit is the next batch of it, so that every thread
 //    has kUnroll vectors in flight.  With a chunk a unit, 2 KiB chunks kept
 //    half the threads idle: 138 us instead of 100 for 1069 spills and 954
-//    restores of 128 KiB blocks, and 80 instead of 31 us at 1 KiB.
+//    restores of 128 KiB blocks, and 80 instead of 31 us at 1 KiB.  Larger
+//    chunks, whose last batch was a short one, gain too: 11 to 17 % at
+//    20 KiB + 16 B, 3 to 7 % at 34 KiB, 5 to 8 % at 66 KiB, 1 to 5 % at
+//    130 KiB, 1 to 3 % at 1 MiB + 4 KiB.
 struct Units {
   int g, lg, per_move;  // chunks per unit (1 but for groups), shape (groups: log2(vectors per
                         // chunk / kBlock)), units per block
@@ -153,6 +156,15 @@ struct RunWalk {
   __device__ __forceinline__ long long at(const cascade_kv_pool_t &pool) const {
     return (long long)(r >> 1) * pool.layer_stride + ((r & 1) ? pool.kv_stride : 0) +
            (long long)off * 16;
+  }
+  // The same place, which the compiler does not know to be the same: else it
+  // keeps every place between the loads and the stores, in registers that the
+  // fused kernel at eight waves has not got (it spilled to scratch memory; 106.9
+  // -> 105.6 us for 1069 spills and 954 restores of 2 KiB chunks without).
+  __device__ __forceinline__ RunWalk again() const {
+    RunWalk w = *this;
+    asm volatile("" : "+v"(w.r), "+v"(w.off));
+    return w;
   }
   __device__ __forceinline__ void next(const Units &un, unsigned dr, unsigned doff) {
     r += dr;
@@ -198,7 +210,7 @@ __device__ __forceinline__ void copy_run(const cascade_kv_pool_t &pool, int slot
                    : sb + (in ? t + u * kBlock : 0));
     w.next(un, dr, doff);
   }
-  w = start;
+  w = start.again();
 #pragma unroll
   for (int u = 0; u < kUnroll; ++u) {
     if (t + u * kBlock < count)
@@ -237,7 +249,7 @@ __device__ __forceinline__ void copy_pair_run(const cascade_kv_pool_t &pool, int
 #pragma unroll
     for (int u = 0; u < kHalf; ++u)
       if (i0 + u * kBlock < count) __builtin_nontemporal_store(a[u], ob + i0 + u * kBlock);
-    w = start;
+    w = start.again();
 #pragma unroll
     for (int u = 0; u < kHalf; ++u) {
       if (i0 + u * kBlock < count)
@@ -299,8 +311,7 @@ __device__ __forceinline__ void copy_pair_group(const cascade_kv_pool_t &pool, i
 
 // The unit shape is a template parameter of the kernels, so each compiled
 // kernel holds one copy path: kRun, kWhole, else a group of g = kUnroll >> kLg
-// chunks.  `first` is the unit's number in the block's
-// run, or its first chunk.
+// chunks.  `first` is the unit's number in the block's run, or its first chunk.
 template <bool kToStaging, int kLg>
 __device__ __forceinline__ void copy_unit(const cascade_kv_pool_t &pool, int slot, char *stg,
                                           int sslot, int first, const Units &un) {
@@ -339,11 +350,11 @@ __device__ __forceinline__ void flag_bad(int *status) {
 }
 
 template <bool kToStaging, int kLg>
-__device__ __forceinline__ void copy_moves(const cascade_kv_pool_t &pool, const Units &un,
-                                           char *staging, int staging_slots,
-                                           const cascade_move_t *__restrict__ moves,
-                                           const int *__restrict__ n_dev, int first,
-                                           int max_moves, int *status) {
+__global__ __launch_bounds__(kBlock) void kvcopy_kernel(cascade_kv_pool_t pool, Units un,
+                                                        char *staging, int staging_slots,
+                                                        const cascade_move_t *__restrict__ moves,
+                                                        const int *__restrict__ n_dev,
+                                                        int first, int max_moves, int *status) {
   // moves points at entry `first` of a list of *n_dev entries
   const int nm = min(*n_dev - first, max_moves);
   if (nm <= 0) return;
@@ -364,25 +375,6 @@ __device__ __forceinline__ void copy_moves(const cascade_kv_pool_t &pool, const 
   }
 }
 
-template <bool kToStaging, int kLg>
-__global__ __launch_bounds__(kBlock) void kvcopy_kernel(cascade_kv_pool_t pool, Units un,
-                                                        char *staging, int staging_slots,
-                                                        const cascade_move_t *__restrict__ moves,
-                                                        const int *__restrict__ n_dev,
-                                                        int first, int max_moves, int *status) {
-  copy_moves<kToStaging, kLg>(pool, un, staging, staging_slots, moves, n_dev, first, max_moves,
-                              status);
-}
-template <bool kToStaging>
-__global__ __launch_bounds__(kBlock) void run_copy_kernel(cascade_kv_pool_t pool, Units un,
-                                                          char *staging, int staging_slots,
-                                                          const cascade_move_t *__restrict__ moves,
-                                                          const int *__restrict__ n_dev,
-                                                          int first, int max_moves, int *status) {
-  copy_moves<kToStaging, kRun>(pool, un, staging, staging_slots, moves, n_dev, first, max_moves,
-                               status);
-}
-
 // Pack and unpack chunks interleaved: the common range holds one pack and
 // one unpack chunk per item pair, the rest belongs to the longer list.
 // Unpack move m paired with pack move j (phz[j] == m and uhz[m] == j) is
@@ -391,9 +383,13 @@ __global__ __launch_bounds__(kBlock) void run_copy_kernel(cascade_kv_pool_t pool
 // overwrites them: the wait is inside the thread, none crosses workgroups.
 // The pairing test reads the same two words from both sides, so every
 // unpack move is copied exactly once.
+// Eight waves per SIMD: the prefetched move words would otherwise push the
+// scalar registers past what eight waves can hold, and at seven the copy
+// moves about 2 % fewer bytes per second (the prefetch gains about 1 % at
+// eight, measured on MI355X).
 template <int kLg>
-__device__ __forceinline__ void move_both(
-    const cascade_kv_pool_t &pool, const Units &un, char *pst, int pst_slots,
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8, 8))) void kvmove_kernel(
+    cascade_kv_pool_t pool, Units un, char *pst, int pst_slots,
     const cascade_move_t *__restrict__ pm, const int *__restrict__ pn_dev, int pmax,
     const int *__restrict__ phz, char *ust, int ust_slots, const cascade_move_t *__restrict__ um,
     const int *__restrict__ un_dev, int umax, const int *__restrict__ uhz, int *status) {
@@ -474,29 +470,6 @@ __device__ __forceinline__ void move_both(
   }
 }
 
-// Eight waves per SIMD: the prefetched move words would otherwise push the
-// scalar registers past what eight waves can hold, and at seven the copy
-// moves about 2 % fewer bytes per second (the prefetch gains about 1 % at
-// eight, measured on MI355X).
-template <int kLg>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8, 8))) void kvmove_kernel(
-    cascade_kv_pool_t pool, Units un, char *pst, int pst_slots,
-    const cascade_move_t *__restrict__ pm, const int *__restrict__ pn_dev, int pmax,
-    const int *__restrict__ phz, char *ust, int ust_slots, const cascade_move_t *__restrict__ um,
-    const int *__restrict__ un_dev, int umax, const int *__restrict__ uhz, int *status) {
-  move_both<kLg>(pool, un, pst, pst_slots, pm, pn_dev, pmax, phz, ust, ust_slots, um, un_dev, umax,
-                 uhz, status);
-}
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8, 8))) void
-run_move_kernel(
-    cascade_kv_pool_t pool, Units un, char *pst, int pst_slots,
-    const cascade_move_t *__restrict__ pm, const int *__restrict__ pn_dev, int pmax,
-    const int *__restrict__ phz, char *ust, int ust_slots, const cascade_move_t *__restrict__ um,
-    const int *__restrict__ un_dev, int umax, const int *__restrict__ uhz, int *status) {
-  move_both<kRun>(pool, un, pst, pst_slots, pm, pn_dev, pmax, phz, ust, ust_slots, um, un_dev,
-                  umax, uhz, status);
-}
-
 bool pool_ok(const cascade_kv_pool_t *p) {
   if (!p || !p->base || p->num_layers < 1 || p->num_slots < 0) return false;
   if (p->chunk_bytes < 16 || (p->chunk_bytes & 15) || p->chunk_bytes > (1ll << 30)) return false;
@@ -540,7 +513,7 @@ int launch(const cascade_kv_pool_t *pool, const void *staging, int32_t staging_s
     return CASCADE_EINVAL;
   if (max_moves == 0) return CASCADE_OK;
   const Units u = units_for(pool);
-  auto kernel = u.lg == kRun     ? run_copy_kernel<kToStaging>
+  auto kernel = u.lg == kRun     ? kvcopy_kernel<kToStaging, kRun>
                 : u.lg == kWhole ? kvcopy_kernel<kToStaging, kWhole>
                 : u.lg == 0      ? kvcopy_kernel<kToStaging, 0>
                 : u.lg == 1      ? kvcopy_kernel<kToStaging, 1>
@@ -595,7 +568,7 @@ extern "C" int cascade_pack_unpack(const cascade_kv_pool_t *pool, void *pack_sta
   if ((max_pack > 0 && !pack_hazard) || (max_unpack > 0 && !unpack_hazard)) return CASCADE_EINVAL;
   if (max_pack == 0 && max_unpack == 0) return CASCADE_OK;
   const Units u = units_for(pool);
-  auto kernel = u.lg == kRun     ? run_move_kernel
+  auto kernel = u.lg == kRun     ? kvmove_kernel<kRun>
                 : u.lg == kWhole ? kvmove_kernel<kWhole>
                 : u.lg == 0      ? kvmove_kernel<0>
                 : u.lg == 1      ? kvmove_kernel<1>

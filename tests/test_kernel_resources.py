@@ -1,8 +1,7 @@
 """Resource use of the library's kernels (no GPU), read from the compiler's
 resource-usage remarks of a gfx950 build: the HBM-bound copy kernels must
 keep the full 8 waves per SIMD, since every wave in flight holds part of the
-bytes the copy needs to cover HBM latency; the latency-bound kernels must not
-use scratch memory."""
+bytes the copy needs to cover HBM latency; no kernel may use scratch memory."""
 import os
 import re
 import shutil
@@ -32,9 +31,10 @@ def test_copy_kernels_keep_full_occupancy(tmp_path):
         if m and name:
             occ[name] = int(m.group(1))
     kernels = {k: v for k, v in occ.items() if "kvcopy_kernel" in k or "kvmove_kernel" in k}
-    # pack and unpack (kvcopy) and the fused launch (kvmove), each in four
-    # unit shapes: whole chunks, and groups of 8, 4 or 2 chunks
-    assert len(kernels) == 12, occ
+    # pack and unpack (kvcopy) and the fused launch (kvmove), each in five
+    # unit shapes: whole chunks, groups of 8, 4 or 2 chunks, and runs; no
+    # kernel of the file is left out
+    assert len(kernels) == 15 and len(occ) == 15, occ
     assert all(v == 8 for v in kernels.values()), kernels
 
 
@@ -58,11 +58,13 @@ def _resource_remarks(src, tmp_path):
 
 
 @pytest.mark.skipif(shutil.which("hipcc") is None, reason="hipcc not installed")
-@pytest.mark.parametrize("src", ["cascade_step.hip", "cascade_reclaim.hip", "cascade_prefix.hip"])
+@pytest.mark.parametrize("src", ["cascade_step.hip", "cascade_reclaim.hip", "cascade_prefix.hip",
+                                 "cascade_kvcopy.hip"])
 def test_latency_bound_kernels_use_no_scratch(src, tmp_path):
     """The step's kernels run on dependent round trips: a private array or
     a spill placed in scratch memory adds a round trip of its own (as a
-    non-inlined device function or an array of HIP vector types can)."""
+    non-inlined device function or an array of HIP vector types can).  In the
+    copy kernels it would take bandwidth from the copy."""
     scratch = _resource_remarks(os.path.join(ROOT, "paper_2608_06557_amd", "csrc", src), tmp_path)
     assert scratch, "no resource remarks"
     assert all(v == 0 for v in scratch.values()), {k: v for k, v in scratch.items() if v}
