@@ -1155,7 +1155,7 @@ static_assert(kBucketCap >= (kTiledTiles + samples_of(256)) * 256 / samples_of(2
 // is only trustworthy after eval.
 template <int kS>
 __global__ __launch_bounds__(kBlock) void split_kernel(
-    int n, int num_blocks, int p, const Partial *__restrict__ partials,
+    int n, int num_blocks, int p, KeySpec spec, const Partial *__restrict__ partials,
     const int *__restrict__ ro, const int *__restrict__ slots, Ctl *ctl, int *info,
     const unsigned long long *__restrict__ samples, int per,
     unsigned long long *__restrict__ splitters) {
@@ -1173,6 +1173,9 @@ __global__ __launch_bounds__(kBlock) void split_kernel(
   for (int j = 0; j < kOwnSamples; ++j) own[j] = samples[g * kOwnSamples + j];
   EvalTotals tot;
   const bool bad_data = eval_totals(p, partials, ctl, info, s_red, tot);
+  // a budget outside the host's range would have run into other bits of its key
+  if (g == 0 && t == 0 && !bad_data && (tot.bmin < spec.lo || tot.bmax - spec.lo >= spec.span))
+    set_status(info, CASCADE_EINTERNAL);
 
   // block-table slots: requested here, checked after the ranks
   const int nnz = bad_data ? 0 : ro[n];
@@ -3497,7 +3500,7 @@ int step_impl(const cascade_requests_t *rq, const cascade_block_table_t *bt,
                        keys_a, rec, o, spec, samples);
     hipLaunchKernelGGL(T <= 512 ? split_kernel<samples_of(512)> : split_kernel<samples_of(1024)>,
                        dim3(tiles * samples_of(T) / kOwnSamples), dim3(kBlock), 0, s, n,
-                       ts->num_blocks, tiles, partials, bt->row_offsets, bt->slots, ctl,
+                       ts->num_blocks, tiles, spec, partials, bt->row_offsets, bt->slots, ctl,
                        out->info, samples, samples_of(T), splitters);
     hipLaunchKernelGGL(T == 256   ? bucket_kernel<256>
                        : T == 512 ? bucket_kernel<512>

@@ -95,3 +95,40 @@ def test_which_tiles_grant(dev, n, cap, reserve):  # noqa: F811
     w = helpers.random_workload(rng, n, params=p, n_free=n // 3)
     g, o = run_both(dev, w)
     assert_same(g, o, f"n={n} cap={cap}")
+
+
+def _widest_clock(w):
+    """The largest t_now_ns at which every key of the queue still fits 63 bits
+    beside its index, from the documented bounds: budgets lie between
+    -(largest latency estimate + t_now) and the largest target, in three
+    priority groups."""
+    p, n = w["params"], len(w["id"])
+    nmax, idx_bits = 1 << 17, (n - 1).bit_length()
+    per_iter = p["c_iter_ps"] + (p["max_batch"] - 1) * p["c_decode_ps"]
+    prefill = (-(-nmax // p["chunk_tokens"]) * per_iter + nmax * p["c_token_ps"] +
+               p["c_attn_ps"] * (nmax * (nmax + 1) // 2))
+    compute_ns = max(prefill, nmax * per_iter) // 1000 + 1
+    restore = sum(p["link_delta_ns"]) + nmax * sum(p["link_blk_ns"])
+    latency = (2 * (compute_ns + restore) * p["gamma_q16"] >> 17) + 1
+    # 3 (hi - lo) + 2 < 2^(63 - idx_bits)
+    return (2 ** (63 - idx_bits) - 3) // 3 - latency - max(p["slo_ns"])
+
+
+@pytest.mark.parametrize("past", [0, 1])
+@pytest.mark.parametrize("n", [1025, 4096, 70000, 200000])
+def test_both_sides_of_the_key_width(dev, n, past):  # noqa: F811
+    """The last clock at which key and index share a word and the first at
+    which they do not, with waits from none to the whole clock, so that
+    budgets lie at both ends of their range; a third of the waits repeat."""
+    import paper_2608_06557_amd.synth as synth
+    w = synth.make_workload(2, seed=n + past, n=n)
+    now = _widest_clock(w) + past
+    assert 0 < now < 2 ** 62
+    rng = np.random.default_rng(n)
+    wait = np.where(np.arange(n) % 3 == 0, rng.integers(0, 20, n) * (now // 20),
+                    (rng.random(n) ** 4 * now).astype(np.int64))
+    wait[:8], wait[8:16] = now, 0
+    w["params"]["t_now_ns"] = now
+    w["arrival_ns"] = (now - np.minimum(wait, now)).astype(np.int64)
+    g, o = run_both(dev, w)
+    assert_same(g, o, f"n={n} t_now={now}")
