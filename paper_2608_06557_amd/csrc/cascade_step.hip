@@ -1921,6 +1921,7 @@ __device__ __forceinline__ unsigned long long granted_before(const unsigned long
           *timed_out = true;
           return sum;
         }
+        __builtin_amdgcn_s_sleep(1);  // up to 255 other waves poll the same few lines
       }
       sum += v >> 2;
 #pragma unroll
