@@ -11,8 +11,8 @@
 //
 // The index is an open-addressing hash table of 16-byte slots (key, set of
 // tiers holding the block) in device memory (index_table.h); key 0 marks an
-// empty slot.  Insert claims a slot by its tier set and then
-// stores the key; the block's deepest tier is the highest tier in its set.
+// empty slot.  Insert claims a slot with a 64-bit CAS on the key and adds the
+// tier to the set; the block's deepest tier is the highest tier in its set.
 // The probe gives each request one wave, which looks up its leading blocks
 // in windows that grow while every block hits; a ballot finds the first miss
 // (a block absent, or whose set is empty), and the wave stops there.  Very long
@@ -37,19 +37,26 @@ __global__ __launch_bounds__(kBlock) void index_clear_kernel(uint4 *slots, long 
     slots[j] = make_uint4(0, 0, 0, 0);
 }
 
-// One thread per (hash, tier) fact.  Random device atomics bound it: about 25 G
-// of them a second against 50 G random reads, and a second atomic on a slot is
-// dearer than the first, since by then hundreds of thousands of other lines
-// have passed through the L2s.  So a new block costs one atomic: it claims a
-// slot whose key is 0 by setting the slot's tier set with a compare-and-swap
-// from 0, then stores its key.  (Only a new block's slot has key 0: a slot whose
-// set was emptied keeps its key.)  A fact already known (its key and its tier
-// there) costs the read alone.  A lane that loses a claim looks at the slot
-// again until the winner's key is there; the winner stores it in the same round
-// that claims, and the round's exit is uniform over the wave, so the key is on
-// its way before any lane of the wave can look again.
-// 1.85 M facts (1.3 M blocks) into 4 M empty slots: CAS on the key then
-// atomicOr of the tier 204 us, with a read first 134 us, this 105 us.
+// One thread per (hash, tier) fact.  A new block claims its slot by a CAS on the
+// key and then stores its tier: nobody else writes a claimed slot's set before
+// that store is there, so it needs no atomic.  The others that find the key add
+// their tier with atomicOr once the set holds a tier (no insert takes one out) or
+// the slot has the mark of a reclamation, and look again until then.  A wave's
+// claims are stored before any of its lanes waits for a tier, and none waits on
+// the way to its slot, so every wait ends.
+// Random device atomics run at about 25 G a second, reads at 50 G, and a second
+// atomic on a slot is dearer than the first, since by then hundreds of thousands
+// of other lines have passed through the L2s.  So many facts (kLook) read a slot
+// before they claim it, and a known fact costs the read alone: 1.85 M facts into
+// an empty index, 30 % of them second tiers, 140 us (CAS then atomicOr 200), when
+// all are known 41 (197).  Few facts are bound by the chain of round trips and
+// claim at once, their tiers stored behind the chain, which would wait for them:
+// into an empty index of twice their number and one of 4 M slots, 1000 facts take
+// 7.4 and 5.4 us (reading first 11.4 and 5.7, CAS then atomicOr 6.8 and 5.1), 8400
+// 5.6 and 5.8 (7.8, 5.7; 5.3, 5.2), 115000 18.3 and 10.9 (22.7, 14.7; 19.4, 12.4),
+// 300000 21.3 and 23.4 (26.7, 33.8; 30.3, 28.5).  Both ways may work on one index
+// at the same time.
+template <bool kLook>
 __global__ __launch_bounds__(kBlock) void index_insert_kernel(IndexSlot *slots, unsigned mask,
                                                               const unsigned long long *hashes,
                                                               const uint8_t *tiers, int n,
@@ -62,32 +69,54 @@ __global__ __launch_bounds__(kBlock) void index_insert_kernel(IndexSlot *slots, 
   if (in && done && status) store_agent(status, (int)CASCADE_EINVAL);
   const unsigned bit = done ? 0u : 1u << t;
   unsigned s = (unsigned)fmix64(h) & mask, p = 0, polls = 0;
-  while (__ballot(!done) != 0) {  // uniform over the wave
+  unsigned long long set = 0ull;  // of the slot whose key is h, as far as known
+  bool claimed = false;
+  while (!done) {  // to the key's slot: no lane waits for another here
+    IndexSlot *e = slots + s;
+    unsigned long long k = 0ull;
+    if (kLook) {
+      k = load_agent(&e->key);
+      set = load_agent(&e->set_word);
+    }
+    if (k == 0ull) {
+      k = atomicCAS(&e->key, 0ull, h);
+      claimed = k == 0ull;
+      set = 0ull;
+      if (kLook && claimed) store_agent(&e->tiers, bit);
+    }
+    if (claimed || k == h) break;
+    if (p == mask) {  // every slot holds another key
+      if (status) store_agent(status, (int)CASCADE_ENOSPC);
+      done = true;
+    }
+    ++p;
+    s = (s + 1) & mask;
+  }
+  IndexSlot *e = slots + s;
+  if (claimed) {
+    if (!kLook) store_agent(&e->tiers, bit);
+    done = true;
+  }
+  while (__ballot(!done) != 0) {  // uniform over the wave: its own claims are stored
     if (!done) {
-      IndexSlot *e = slots + s;
-      const unsigned long long k = load_agent(&e->key);
-      const unsigned set = load_agent(&e->tiers);
-      if (k == 0ull) {
-        if (set == 0u && atomicCAS(&e->tiers, 0u, bit) == 0u) {
-          store_agent(&e->key, h);
-          done = true;
-        } else if (++polls > kSpinLimit) {  // never, unless the memory is no index
-          if (status) store_agent(status, (int)CASCADE_EINTERNAL);
-          done = true;
-        }
-      } else if (k == h) {
-        if (!(set & bit)) atomicOr(&e->tiers, bit);
+      if ((unsigned)set & bit) {
         done = true;
-      } else if (p == mask) {  // every slot holds another key
-        if (status) store_agent(status, (int)CASCADE_ENOSPC);
+      } else if (set != 0ull || ++polls > kSpinLimit) {
+        // the bound is for index memory whose emptied slots have no mark
+        atomicOr(&e->tiers, bit);
         done = true;
       } else {
-        ++p;
-        s = (s + 1) & mask;
+        set = kLook ? load_agent(&e->set_word) : atomicCAS(&e->set_word, 0ull, 0ull);
       }
     }
   }
 }
+
+// Facts from which on the slot is read first.  Facts that are all known already
+// are faster so from a few thousand on (115000: 4.7 against 11.4 us), new ones only
+// in an index that they fill (520000 into 1 M slots 52 against 60 us, into 4 M 53
+// against 41).  From here on neither is slower than CAS then atomicOr (77 and 53).
+constexpr int kLookFacts = 1 << 19;
 
 // Lookups per lane in a probe window, at most: the window doubles from 64
 // blocks (one per lane) up to 64 * kProbeMaxK.
@@ -438,7 +467,8 @@ extern "C" int cascade_prefix_index_insert(void *index, int32_t capacity, const 
   if (!index || !capacity_ok(capacity) || ((uintptr_t)index & 15) || n < 0) return CASCADE_EINVAL;
   if (n == 0) return CASCADE_OK;
   if (!hashes || !tiers) return CASCADE_EINVAL;
-  hipLaunchKernelGGL(index_insert_kernel, dim3((n + kBlock - 1) / kBlock), dim3(kBlock), 0,
+  hipLaunchKernelGGL(n < kLookFacts ? index_insert_kernel<false> : index_insert_kernel<true>,
+                     dim3((n + kBlock - 1) / kBlock), dim3(kBlock), 0,
                      static_cast<hipStream_t>(stream), static_cast<IndexSlot *>(index),
                      (unsigned)(capacity - 1), reinterpret_cast<const unsigned long long *>(hashes),
                      tiers, n, status_dev);

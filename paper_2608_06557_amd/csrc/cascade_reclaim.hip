@@ -1436,7 +1436,11 @@ __device__ __forceinline__ void write_tile(const RcArgs &a, int tile) {
       a.outgoing[q] = d;
       if (ix) atomicOr(&ix->tiers, 1u << (a.tier + 1));
     }
-    if (ix) atomicAnd(&ix->tiers, ~(1u << a.tier));
+    if (ix) {
+      atomicAnd(&ix->tiers, ~(1u << a.tier));
+      // an insert may find the set empty now (a demoted block has its next tier)
+      if (!dem) atomicOr(&ix->emptied, 1u);
+    }
     if (!place) {
       a.freed[p] = slot;
       a.hash[slot] = 0ull;

@@ -2,10 +2,11 @@
 // lookup (cascade_prefix.hip) and the per-tier reclamation
 // (cascade_reclaim.hip).  Internal to the library.
 //
-// Slot = (key, tiers): key is a block's nonzero prefix hash (0 = empty slot),
+// Slot = (key, tiers, mark): key is a block's nonzero prefix hash (0 = empty slot),
 // tiers the set of tiers holding the block (bit k = tier k).  The block's
 // deepest tier is the highest set bit; an empty set means no tier holds it
-// any more (the key stays, so probe sequences stay intact).  Linear probing
+// any more (the key stays, so probe sequences stay intact, and a mark tells the
+// set from that of a slot just claimed, whose tier is on its way).  Linear probing
 // from the murmur3 64-bit finalizer of the key.
 #pragma once
 #include <hip/hip_runtime.h>
@@ -17,8 +18,13 @@ namespace cascade {
 
 struct alignas(16) IndexSlot {
   unsigned long long key;  // block hash, 0 = empty
-  unsigned tiers;          // bit k set = tier k holds the block
-  unsigned pad;
+  union {
+    struct {
+      unsigned tiers;    // bit k set = tier k holds the block
+      unsigned emptied;  // 1 once a reclamation may have emptied the set
+    };
+    unsigned long long set_word;  // both
+  };
 };
 static_assert(sizeof(IndexSlot) == CASCADE_INDEX_SLOT_BYTES, "slot layout");
 

@@ -303,3 +303,107 @@ def test_insert_contended_and_repeated(dev):
         want[h] = want.get(h, 0) | 1 << t
     assert all(sets[h] == w for h, w in want.items())
     assert (slots[:, 1][slots[:, 0] == 0] == 0).all()
+
+
+# facts from which on an insert reads a slot before it claims it
+LOOK_FACTS = 1 << 19
+
+
+def _insert(dev, index, capacity, hashes, tiers, status, stream=None):
+    import paper_2608_06557_amd.cascade as cx
+    assert cx.cascade_prefix_index_insert(index.data_ptr(), capacity, hashes.data_ptr(),
+                                          tiers.data_ptr(), len(tiers), status.data_ptr(),
+                                          dev.stream_handle(stream)) == 0
+
+
+def _facts(rng, keys, n):
+    """n facts on the keys, every key among them, and each key's tier set."""
+    k = np.concatenate([np.arange(len(keys)), rng.integers(0, len(keys), n - len(keys))])
+    t = rng.integers(0, 3, n).astype(np.uint8)
+    order = rng.permutation(n)
+    want = np.zeros(len(keys), np.uint32)
+    np.bitwise_or.at(want, k, np.uint32(1) << t)
+    return (torch.from_numpy(keys[k][order].view(np.int64)).cuda(),
+            torch.from_numpy(t[order]).cuda(), want)
+
+
+def _assert_contents(dev, index, keys, want):
+    got_keys, got_sets = dev.index_contents(index.cpu().numpy())
+    order = np.argsort(keys)
+    assert np.array_equal(got_keys, keys[order])
+    assert np.array_equal(got_sets, want[order])
+
+
+@pytest.mark.parametrize("n", [200, 5000, LOOK_FACTS - 1, LOOK_FACTS])
+def test_insert_both_ways(dev, n):
+    """Several facts per key, most of them on their way at the same time, into
+    a table filled to 9/10, then all of them again."""
+    rng = np.random.default_rng(n)
+    cap = 1 << (max(n // 3, 64) - 1).bit_length()
+    keys = np.unique(rng.integers(1, 1 << 63, int(cap * 0.9), dtype=np.uint64))[:n]
+    h, t, want = _facts(rng, keys, n)
+    index = torch.zeros(cap * 16, dtype=torch.uint8, device="cuda")
+    status = torch.zeros(1, dtype=torch.int32, device="cuda")
+    for _ in range(2):
+        _insert(dev, index, cap, h, t, status)
+        assert int(status.item()) == 0
+        _assert_contents(dev, index, keys, want)
+    assert (index.view(torch.int32)[3::4] == 0).all()     # nothing was reclaimed
+
+
+def test_inserts_of_both_ways_at_once(dev):
+    """One long insert and many short ones on other streams, which share keys
+    and slots with it: the union of their facts."""
+    rng = np.random.default_rng(5)
+    cap = 1 << 19
+    keys = np.unique(rng.integers(1, 1 << 63, 400_000, dtype=np.uint64))
+    h, t, want = _facts(rng, keys, LOOK_FACTS + 77)
+    short = [_facts(rng, keys[rng.permutation(len(keys))[:3000]], 4000) for _ in range(24)]
+    by_key = dict(zip(keys.tolist(), range(len(keys))))
+    for sh, st, _ in short:
+        at = [by_key[k] for k in sh.cpu().numpy().view(np.uint64).tolist()]
+        np.bitwise_or.at(want, at, np.uint32(1) << st.cpu().numpy())
+    index = torch.zeros(cap * 16, dtype=torch.uint8, device="cuda")
+    status = torch.zeros(1, dtype=torch.int32, device="cuda")
+    streams = [torch.cuda.Stream() for _ in range(3)]
+    torch.cuda.synchronize()
+    _insert(dev, index, cap, h, t, status, streams[0])
+    for k, (sh, st, _) in enumerate(short):
+        _insert(dev, index, cap, sh, st, status, streams[1 + k % 2])
+    torch.cuda.synchronize()
+    assert int(status.item()) == 0
+    _assert_contents(dev, index, keys, want)
+
+
+@pytest.mark.parametrize("per_key,capacity", [(3, 1 << 16), (60, 1 << 20)])
+def test_insert_into_reclaimed_sets(dev, per_key, capacity):
+    """Blocks whose last copy a reclamation took come back, beside new blocks
+    that probe past their slots.  The reclamation marks every slot it took a
+    tier from, so that an insert knows an empty set from one whose first tier
+    is on its way."""
+    import paper_2608_06557_amd.synth as synth
+    w = synth.make_tier_workload(2, seed=21, sizes=(2000, 9000, 30_000), needs=(700, 400, 3000))
+    d = dev.DeviceTiers(w["tables"], w["needs"], w["index_keys"], w["index_masks"],
+                        capacity=capacity)
+    assert d.run_chain() == 0
+    torch.cuda.synchronize()
+    keys, sets = dev.index_contents(d.index.cpu().numpy())
+    gone = keys[sets == 0]
+    assert len(gone) > 1000
+    words = d.index.cpu().numpy().view(np.uint32).reshape(-1, 4)
+    occupied = (words[:, 0] | words[:, 1]) != 0
+    assert (words[occupied & (words[:, 2] == 0), 3] == 1).all()
+    rng = np.random.default_rng(per_key)
+    new = np.setdiff1d(rng.integers(1, 1 << 63, 9000, dtype=np.uint64), keys)
+    back = np.concatenate([gone, new])
+    n = per_key * len(back)
+    assert (n >= LOOK_FACTS) == (per_key > 3)
+    h, t, want = _facts(rng, back, n)
+    _insert(dev, d.index, d.capacity, h, t, d.status)
+    torch.cuda.synchronize()
+    assert int(d.status.item()) == 0
+    old = dict(zip(keys.tolist(), sets.tolist()))
+    old.update(zip(back.tolist(), want.tolist()))
+    all_keys = np.array(sorted(old), np.uint64)
+    _assert_contents(dev, d.index, all_keys,
+                     np.array([old[k] for k in all_keys.tolist()], np.uint32))
