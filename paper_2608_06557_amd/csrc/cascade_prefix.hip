@@ -248,15 +248,23 @@ __device__ __forceinline__ int window_end(int b) {
 // Lookups of one request by `nw` waves of a workgroup (`g0` the first of them),
 // from block `base` (a window's start, every earlier block cached): rounds of nw
 // adjacent windows of 64 * kProbeMaxK blocks, one per wave, until a round holds
-// a miss or the request ends.  Every wave of the workgroup calls it (lim 0: no
-// request), and a round's one barrier is also what ends the loop for all of them
-// at once.  Returns the run's length; s_round holds the answers of two rounds.
-// bad (a hash 0 that counts) is complete in the first wave, which reports it.
+// a miss or the request ends.  From block 0 (kStart, every wave of the workgroup)
+// the first round of a prompt of up to kShortBlocks has windows of 64: it need not
+// wait for the slots of blocks far behind its miss.  64 chat requests 4.1 us, with
+// windows of 256 for every prompt 6.8, in one wave each 4.7; 256 of them 4.7, 8.6
+// and 6.2.  For longer prompts it is a round more (512 chat and agentic requests
+// 12.2 us, 16.0 with windows of 64 first for every prompt).  Every wave of the
+// workgroup calls it (lim 0: no request), and a round's one barrier is also what
+// ends the loop for all of them at once.  Returns the run's length; s_round holds
+// the answers of two rounds.  bad (a hash 0 that counts) is complete in the first
+// wave, which reports it.
+constexpr int kShortBlocks = 512;
 struct WaveAnswer {
   int miss, zero;  // first missing block, first hash 0 (INT_MAX: none)
   unsigned deepest;
   int active;      // the wave's request was not decided before this round
 };
+template <bool kStart>
 __device__ __forceinline__ int probe_wide(const uint4 *__restrict__ sl, unsigned mask,
                                           const unsigned long long *__restrict__ hb, int lim,
                                           int base, int g0, int nw,
@@ -264,28 +272,32 @@ __device__ __forceinline__ int probe_wide(const uint4 *__restrict__ sl, unsigned
                                           bool &bad) {
   constexpr int K = kProbeMaxK, win = 64 * K;
   const int lane = lane_id(), wave = wave_id();
-  unsigned long long h[K];
-  int wb = base + (wave - g0) * win, run = 0, first_zero = INT_MAX;
+  unsigned long long h[K], h0[1] = {0ull};
+  bool active = base < lim, start = kStart && lim <= kShortBlocks;
+  int wb = base + (start ? 64 * nw : 0) + (wave - g0) * win, run = 0, first_zero = INT_MAX;
+  if (start && wave * 64 + lane < lim) h0[0] = hb[wave * 64 + lane];
 #pragma unroll
   for (int u = 0; u < K; ++u) {
     const int j = wb + u * 64 + lane;
     h[u] = j < lim ? hb[j] : 0ull;
   }
-  bool active = base < lim;
   for (int r = 0;; r ^= 1) {  // uniform over the workgroup
     unsigned d = 0u, z = 0u;
-    int first = win, zero = INT_MAX;
-    if (active && wb < lim)  // uniform over the wave
-      first = probe_window<K, K>(sl, mask, hb, lim, wb, wb + nw * win, lane, h, d, z);
+    const int size = start ? 64 : win, at = start ? wave * 64 : wb;
+    int first = size, zero = INT_MAX;
+    if (active && at < lim) {  // uniform over the wave
+      if (start) first = probe_window<1, 1>(sl, mask, hb, lim, at, lim, lane, h0, d, z);
+      else first = probe_window<K, K>(sl, mask, hb, lim, at, at + nw * win, lane, h, d, z);
+    }
     if (__ballot(z != 0u)) {  // invalid input
 #pragma unroll
       for (int u = K - 1; u >= 0; --u) {
         const uint64_t m = __ballot((z >> u) & 1u);
-        if (m) zero = wb + u * 64 + __builtin_ctzll(m);
+        if (m) zero = at + u * 64 + __builtin_ctzll(m);
       }
     }
     if (lane == 0)
-      s_round[r][wave] = {first < win ? wb + first : INT_MAX, zero, d, (int)active};
+      s_round[r][wave] = {first < size ? at + first : INT_MAX, zero, d, (int)active};
     __syncthreads();
     int miss = INT_MAX, any = 0;
 #pragma unroll
@@ -298,8 +310,9 @@ __device__ __forceinline__ int probe_wide(const uint4 *__restrict__ sl, unsigned
       first_zero = min(first_zero, a.zero);
     }
     if (!any) return run;
-    base += nw * win;
-    wb += nw * win;
+    base += nw * size;
+    wb += start ? 0 : nw * win;
+    start = false;
     if (active && (miss != INT_MAX || base >= lim)) {
       if (miss != INT_MAX) {
         // the miss's window may reach past the round: into the hashes that the
@@ -312,6 +325,7 @@ __device__ __forceinline__ int probe_wide(const uint4 *__restrict__ sl, unsigned
       }
       run = miss != INT_MAX ? miss : lim;
       active = false;
+      if (kStart) return run;  // the workgroup's one request
     }
   }
 }
@@ -321,7 +335,8 @@ __device__ __forceinline__ int probe_wide(const uint4 *__restrict__ sl, unsigned
 // short run (most of them) costs one small window, and the wave stops at the
 // first miss: blocks past it in later windows cost nothing.
 // From block kProbeTail on the workgroup's waves share the requests that are left
-// among them: window after window in one wave, the longest runs (5000 blocks)
+// among them, and a workgroup without a prompt that long does not wait for its
+// slowest wave (16384 chat requests 25.1 us, 26.1 with that wait): window after window in one wave, the longest runs (5000 blocks)
 // outlast the rest of the launch.  Chat and agentic prompts, this against every
 // request alone in its wave: 16384 requests 78 against 108 us, 32768 139 against
 // 181, 65536 191 against 208.  Starting to share at block 960 measured 70, 157
@@ -343,9 +358,16 @@ __global__ __launch_bounds__(kBlock, 7) void probe_kernel(const IndexSlot *__res
   const int i = blockIdx.x * kWaves + wave_id();
   const int lane = lane_id();
   const uint4 *sl = reinterpret_cast<const uint4 *>(slots);
+  // lane w: the workgroup's request w.  Only runs that may reach block kProbeTail
+  // make the waves meet there.
   int b0 = 0, lim = 0;
   bool bad = false;
-  if (i < n) lim = request_limit(i, n, offsets, n_in, bt, b0, bad);
+  if (lane < kWaves && i - wave_id() + lane < n)
+    lim = request_limit(i - wave_id() + lane, n, offsets, n_in, bt, b0, bad);
+  const bool meet = __ballot(lim > kProbeTail) != 0;  // uniform over the workgroup
+  bad = (__ballot(bad) >> wave_id()) & 1;
+  lim = __builtin_amdgcn_readlane(lim, __builtin_amdgcn_readfirstlane(wave_id()));
+  b0 = __builtin_amdgcn_readlane(b0, __builtin_amdgcn_readfirstlane(wave_id()));
   const unsigned long long *hb = hashes + b0;
   int matched = 0;
   unsigned deepest = 0, zero = 0;
@@ -382,6 +404,7 @@ __global__ __launch_bounds__(kBlock, 7) void probe_kernel(const IndexSlot *__res
       tier_out[i] = (uint8_t)(matched > 0 ? deepest : (unsigned)CASCADE_KV_NONE);
     }
   }
+  if (!meet) return;
   __syncthreads();
   // m requests are left: the j-th of them takes (kWaves + m - 1 - j) / m waves
   int m = 0, req = -1, g0 = 0, nw = 1;
@@ -402,8 +425,8 @@ __global__ __launch_bounds__(kBlock, 7) void probe_kernel(const IndexSlot *__res
     ++j;
   }
   deepest = s_deep[req];
-  const int run = probe_wide(sl, mask, hashes + s_b0[req], s_lim[req], kProbeTail, g0, nw,
-                             s_round, deepest, bad);
+  const int run = probe_wide<false>(sl, mask, hashes + s_b0[req], s_lim[req], kProbeTail, g0,
+                                    nw, s_round, deepest, bad);
   if (lane == 0 && wave_id() == g0) {
     const int o = blockIdx.x * kWaves + req;
     if (bad && status) store_agent(status, (int)CASCADE_EINVAL);
@@ -414,9 +437,10 @@ __global__ __launch_bounds__(kBlock, 7) void probe_kernel(const IndexSlot *__res
 
 // One workgroup per request, from its first block: every wave's window at once
 // costs lookups past the miss, but few requests leave the chip idle, and then
-// the number of dependent rounds is the time.  64 requests 14 against 25 us one
-// wave each, 1024 37 against 72, 2048 23 against 38.  Longer queues fill the chip:
-// at 8192 short prompts 27 against 17 us (long ones 52 against 48).
+// the number of dependent rounds is the time.  Chat and agentic requests, against
+// one wave each: 64 of them 16 against 21 us, 512 12 against 30, 1024 22 against
+// 45, 2048 30 against 48.  Longer queues fill the chip: at 8192 short prompts 27
+// against 17 us (long ones 52 against 48).
 __global__ __launch_bounds__(kBlock) void probe_wide_kernel(
     const IndexSlot *__restrict__ slots, unsigned mask, int n, const int *__restrict__ offsets,
     const unsigned long long *__restrict__ hashes, const int *__restrict__ n_in, int bt,
@@ -427,9 +451,9 @@ __global__ __launch_bounds__(kBlock) void probe_wide_kernel(
   bool bad;
   const int lim = request_limit(i, n, offsets, n_in, bt, b0, bad);
   unsigned deepest = 0u;
-  const int run = lim <= 0 ? 0 : probe_wide(reinterpret_cast<const uint4 *>(slots), mask,
-                                            hashes + b0, lim, 0, 0, kWaves, s_round, deepest,
-                                            bad);
+  const int run = lim <= 0 ? 0 : probe_wide<true>(reinterpret_cast<const uint4 *>(slots),
+                                                  mask, hashes + b0, lim, 0, 0, kWaves, s_round,
+                                                  deepest, bad);
   if (threadIdx.x == 0) {
     if (bad && status) store_agent(status, (int)CASCADE_EINVAL);
     n_prefix_out[i] = run * bt;
@@ -494,8 +518,8 @@ extern "C" int cascade_prefix_probe(const void *index, int32_t capacity, int32_t
                        block_offsets, hashes, n_in, block_tokens, n_prefix_out, prefix_tier_out,
                        status_dev);
   } else {
-    hipLaunchKernelGGL(probe_kernel, dim3((n + kWaves - 1) / kWaves), dim3(kBlock), 0, s, slots, mask, n,
-                       block_offsets, hashes, n_in, block_tokens, n_prefix_out, prefix_tier_out,
+    hipLaunchKernelGGL(probe_kernel, dim3((n + kWaves - 1) / kWaves), dim3(kBlock), 0, s, slots,
+                       mask, n, block_offsets, hashes, n_in, block_tokens, n_prefix_out, prefix_tier_out,
                        status_dev);
   }
   return hipGetLastError() == hipSuccess ? CASCADE_OK : CASCADE_EHIP;

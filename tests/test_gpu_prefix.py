@@ -407,3 +407,35 @@ def test_insert_into_reclaimed_sets(dev, per_key, capacity):
     all_keys = np.array(sorted(old), np.uint64)
     _assert_contents(dev, d.index, all_keys,
                      np.array([old[k] for k in all_keys.tolist()], np.uint32))
+
+
+@pytest.mark.parametrize("n", [18, 2048, 2049])
+def test_short_prompts(dev, n):
+    """Prompts around 512 blocks, up to which a workgroup's first round looks
+    at 4 x 64 blocks and above at 4 x 256, and runs that end at the edges of
+    the windows."""
+    edges = [0, 1, 63, 64, 65, 127, 128, 191, 192, 193, 255, 256, 257, 447, 448, 510, 511, 512]
+    for length in (70, 256, 511, 512, 513):
+        entries, reqs = _edge_requests([min(e, length) for e in edges], length, 1_000_000)
+        reqs = [reqs[i % len(reqs)] for i in range(n)]
+        g, o, _ = run_both(dev, _pw(entries, reqs))
+        assert_same(g, o, f"{length} blocks")
+        assert int(g["n_prefix"].max()) == 16 * min(length, 512)
+
+
+@pytest.mark.parametrize("n", [1, 2500])
+@pytest.mark.parametrize("miss,zero,bad", [
+    (10, 60, True), (10, 64, False), (63, 64, False), (64, 191, True), (191, 192, False),
+    (192, 447, True), (200, 448, False), (255, 447, True), (256, 447, True), (447, 448, False),
+    (448, 499, True), (300, 200, True)])
+def test_zero_hash_past_the_miss_of_a_short_prompt(dev, n, miss, zero, bad):
+    # as for the long prompts above, where the window of the first miss reaches
+    # past the 256 blocks of the first round
+    entries, reqs = _edge_requests([miss], 500, 1_000_000)
+    reqs[0][1][zero] = 0
+    reqs += [(64, [5, 6])] * (n - 1)
+    d = dev.DevicePrefix(_pw(entries, reqs))
+    assert d.build() == 0 and d.probe() == 0
+    g = d.fetch()
+    assert g["status"] == (ref.EINVAL if bad else 0)
+    assert g["n_prefix"][0] == 16 * min(miss, zero) and g["prefix_tier"][0] == (zero > miss)
