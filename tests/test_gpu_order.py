@@ -65,21 +65,38 @@ def test_ordered_and_repeated_waits(dev, how):  # noqa: F811
     assert_same(g, o, how)
 
 
+def _buckets(wait, T, gap):
+    """Keys per bucket of a tiled sort in tiles of T, from which every gap-th
+    key from place 7 * tile mod gap on is sampled and every (T / gap)-th sample
+    taken as a splitter.  Longer waits come first, equal ones in queue order."""
+    n = len(wait)
+    key = (wait.max() - wait) * n + np.arange(n)
+    samples = []
+    for t in range(n // T):
+        tile = np.sort(key[t * T:(t + 1) * T])
+        samples.append(tile[(7 * t) % gap::gap])
+    splitters = np.sort(np.concatenate(samples))[::T // gap]
+    bucket = np.searchsorted(splitters[1:], key, side="right")
+    return np.bincount(bucket, minlength=len(splitters))
+
+
 @pytest.mark.parametrize("pos", [0, 1])
-def test_bucket_beyond_lds(dev, pos):  # noqa: F811
-    """63 of each tile's 1024 keys lie between two of its sampled places (64
-    apart from place 7 * tile mod 64) and in one range over all tiles, so no
-    sample splits that range: 16128 keys in one bucket."""
-    n, T = 262144, 1024
-    rng = np.random.default_rng(11 + pos)
+@pytest.mark.parametrize("n,T", [(131072, 512), (262144, 1024)])
+def test_bucket_beyond_lds(dev, n, T, pos):  # noqa: F811
+    """31 of each tile's keys lie between two of its samples, 32 apart, and in
+    one range over all 256 tiles, so no sample splits that range: 7936 keys in
+    one bucket, more than the 4352 that a workgroup sorts in LDS."""
+    gap, rng = 32, np.random.default_rng(11 + pos)
     wait = np.zeros(n, np.int64)
     for t in range(n // T):
-        first = (7 * t) % 64 + 64 * (7 * pos) + 1     # first place behind a sample
+        first = (7 * t) % gap + gap * (7 * pos) + 1       # first place behind a sample
         v = np.empty(T, np.int64)
-        v[:first] = rng.integers(200, 300, first)      # least budget: longest wait
-        v[first:first + 63] = rng.integers(100, 130, 63)  # ties across all tiles
-        v[first + 63:] = rng.integers(0, 50, T - first - 63)
+        v[:first] = rng.integers(200, 300, first)         # least budget: longest wait
+        v[first:first + gap - 1] = rng.integers(100, 130, gap - 1)  # ties across all tiles
+        v[first + gap - 1:] = rng.integers(0, 50, T - first - gap + 1)
         wait[t * T:(t + 1) * T] = rng.permutation(v)
+    sizes = _buckets(wait, T, gap)
+    assert sizes.sum() == n and sizes.max() >= 31 * 256 > 4352
     g, o = run_both(dev, queued(n, wait * 10 ** 9))
     assert_same(g, o, "overflow")
 
