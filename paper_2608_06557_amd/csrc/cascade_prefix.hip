@@ -248,23 +248,32 @@ __device__ __forceinline__ int window_end(int b) {
 // Lookups of one request by `nw` waves of a workgroup (`g0` the first of them),
 // from block `base` (a window's start, every earlier block cached): rounds of nw
 // adjacent windows of 64 * kProbeMaxK blocks, one per wave, until a round holds
-// a miss or the request ends.  From block 0 (kStart, every wave of the workgroup)
-// the first round of a prompt of up to kShortBlocks has windows of 64: it need not
-// wait for the slots of blocks far behind its miss.  64 chat requests 4.1 us, with
-// windows of 256 for every prompt 6.8, in one wave each 4.7; 256 of them 4.7, 8.6
-// and 6.2.  For longer prompts it is a round more (512 chat and agentic requests
-// 12.2 us, 16.0 with windows of 64 first for every prompt).  Every wave of the
-// workgroup calls it (lim 0: no request), and a round's one barrier is also what
-// ends the loop for all of them at once.  Returns the run's length; s_round holds
-// the answers of two rounds.  bad (a hash 0 that counts) is complete in the first
-// wave, which reports it.
-constexpr int kShortBlocks = 512;
+// a miss or the request ends.  Every wave of the workgroup calls it (lim 0: no
+// request), and a round's one barrier is also what ends the loop for all of them
+// at once; with kOne they share one request, and its last round ends it.  Returns
+// the run's length; s_round holds the answers of two rounds.  bad (a hash 0 that
+// counts) is complete in the first wave, which reports it.
 struct WaveAnswer {
   int miss, zero;  // first missing block, first hash 0 (INT_MAX: none)
   unsigned deepest;
   int active;      // the wave's request was not decided before this round
 };
-template <bool kStart>
+// The answer of a wave's window of K items per lane from block `at`.
+template <int K>
+__device__ __forceinline__ WaveAnswer wave_answer(int at, int first, unsigned z, unsigned deepest,
+                                                  bool active) {
+  int zero = INT_MAX;
+  if (__ballot(z != 0u)) {  // invalid input
+#pragma unroll
+    for (int u = K - 1; u >= 0; --u) {
+      const uint64_t m = __ballot((z >> u) & 1u);
+      if (m) zero = at + u * 64 + __builtin_ctzll(m);
+    }
+  }
+  return {first < 64 * K ? at + first : INT_MAX, zero, deepest, (int)active};
+}
+
+template <bool kOne>
 __device__ __forceinline__ int probe_wide(const uint4 *__restrict__ sl, unsigned mask,
                                           const unsigned long long *__restrict__ hb, int lim,
                                           int base, int g0, int nw,
@@ -272,32 +281,21 @@ __device__ __forceinline__ int probe_wide(const uint4 *__restrict__ sl, unsigned
                                           bool &bad) {
   constexpr int K = kProbeMaxK, win = 64 * K;
   const int lane = lane_id(), wave = wave_id();
-  unsigned long long h[K], h0[1] = {0ull};
-  bool active = base < lim, start = kStart && lim <= kShortBlocks;
-  int wb = base + (start ? 64 * nw : 0) + (wave - g0) * win, run = 0, first_zero = INT_MAX;
-  if (start && wave * 64 + lane < lim) h0[0] = hb[wave * 64 + lane];
+  unsigned long long h[K];
+  int wb = base + (wave - g0) * win, run = 0, first_zero = INT_MAX;
 #pragma unroll
   for (int u = 0; u < K; ++u) {
     const int j = wb + u * 64 + lane;
     h[u] = j < lim ? hb[j] : 0ull;
   }
+  bool active = base < lim;
   for (int r = 0;; r ^= 1) {  // uniform over the workgroup
     unsigned d = 0u, z = 0u;
-    const int size = start ? 64 : win, at = start ? wave * 64 : wb;
-    int first = size, zero = INT_MAX;
-    if (active && at < lim) {  // uniform over the wave
-      if (start) first = probe_window<1, 1>(sl, mask, hb, lim, at, lim, lane, h0, d, z);
-      else first = probe_window<K, K>(sl, mask, hb, lim, at, at + nw * win, lane, h, d, z);
-    }
-    if (__ballot(z != 0u)) {  // invalid input
-#pragma unroll
-      for (int u = K - 1; u >= 0; --u) {
-        const uint64_t m = __ballot((z >> u) & 1u);
-        if (m) zero = at + u * 64 + __builtin_ctzll(m);
-      }
-    }
-    if (lane == 0)
-      s_round[r][wave] = {first < size ? at + first : INT_MAX, zero, d, (int)active};
+    int first = win;
+    if (active && wb < lim)  // uniform over the wave
+      first = probe_window<K, K>(sl, mask, hb, lim, wb, wb + nw * win, lane, h, d, z);
+    const WaveAnswer mine = wave_answer<K>(wb, first, z, d, active);
+    if (lane == 0) s_round[r][wave] = mine;
     __syncthreads();
     int miss = INT_MAX, any = 0;
 #pragma unroll
@@ -309,10 +307,9 @@ __device__ __forceinline__ int probe_wide(const uint4 *__restrict__ sl, unsigned
       miss = min(miss, a.miss);
       first_zero = min(first_zero, a.zero);
     }
-    if (!any) return run;
-    base += nw * size;
-    wb += start ? 0 : nw * win;
-    start = false;
+    if (!kOne && !any) return run;
+    base += nw * win;
+    wb += nw * win;
     if (active && (miss != INT_MAX || base >= lim)) {
       if (miss != INT_MAX) {
         // the miss's window may reach past the round: into the hashes that the
@@ -324,10 +321,44 @@ __device__ __forceinline__ int probe_wide(const uint4 *__restrict__ sl, unsigned
         bad = bad || __ballot(z) != 0;
       }
       run = miss != INT_MAX ? miss : lim;
+      if (kOne) return run;
       active = false;
-      if (kStart) return run;  // the workgroup's one request
     }
   }
+}
+
+// A request of up to kWaves * 64 * K blocks in one round, a window of 64 * K
+// blocks per wave: as probe_wide with kOne.
+template <int K>
+__device__ __forceinline__ int probe_once(const uint4 *__restrict__ sl, unsigned mask,
+                                          const unsigned long long *__restrict__ hb, int lim,
+                                          WaveAnswer (&s_round)[kWaves], unsigned &deepest,
+                                          bool &bad) {
+  const int lane = lane_id(), at = wave_id() * 64 * K;
+  unsigned long long h[K];
+#pragma unroll
+  for (int u = 0; u < K; ++u) {
+    const int j = at + u * 64 + lane;
+    h[u] = j < lim ? hb[j] : 0ull;
+  }
+  unsigned d = 0u, z = 0u;
+  int first = 64 * K;
+  if (at < lim)  // uniform over the wave
+    first = probe_window<K, K>(sl, mask, hb, lim, at, lim, lane, h, d, z);
+  const WaveAnswer mine = wave_answer<K>(at, first, z, d, true);
+  if (lane == 0) s_round[wave_id()] = mine;
+  __syncthreads();
+  int miss = INT_MAX, zero = INT_MAX;
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) {
+    const WaveAnswer a = s_round[w];
+    if (miss == INT_MAX) deepest = max(deepest, a.deepest);  // none past the miss
+    miss = min(miss, a.miss);
+    zero = min(zero, a.zero);
+  }
+  if (miss == INT_MAX) return lim;
+  bad = bad || zero < min(window_end(miss), lim);
+  return miss;
 }
 
 // One wave per request.  Its leading blocks are looked up in windows of
@@ -440,7 +471,10 @@ __global__ __launch_bounds__(kBlock, 7) void probe_kernel(const IndexSlot *__res
 // the number of dependent rounds is the time.  Chat and agentic requests, against
 // one wave each: 64 of them 16 against 21 us, 512 12 against 30, 1024 22 against
 // 45, 2048 30 against 48.  Longer queues fill the chip: at 8192 short prompts 27
-// against 17 us (long ones 52 against 48).
+// against 17 us (long ones 52 against 48).  A prompt of up to 256 or 512 blocks
+// takes one round of windows of 64 or 128: it need not wait for the slots of blocks
+// far behind its miss.  64 chat requests 3.7 us (windows of 256 6.8, one wave each
+// 4.7), 256 4.5 (8.4, 6.2), 2048 6.2 (10.3, 8.6).
 __global__ __launch_bounds__(kBlock) void probe_wide_kernel(
     const IndexSlot *__restrict__ slots, unsigned mask, int n, const int *__restrict__ offsets,
     const unsigned long long *__restrict__ hashes, const int *__restrict__ n_in, int bt,
@@ -450,10 +484,16 @@ __global__ __launch_bounds__(kBlock) void probe_wide_kernel(
   int b0;
   bool bad;
   const int lim = request_limit(i, n, offsets, n_in, bt, b0, bad);
+  const uint4 *sl = reinterpret_cast<const uint4 *>(slots);
+  const unsigned long long *hb = hashes + b0;
   unsigned deepest = 0u;
-  const int run = lim <= 0 ? 0 : probe_wide<true>(reinterpret_cast<const uint4 *>(slots),
-                                                  mask, hashes + b0, lim, 0, 0, kWaves, s_round,
-                                                  deepest, bad);
+  int run = 0;
+  if (lim > kWaves * 128)
+    run = probe_wide<true>(sl, mask, hb, lim, 0, 0, kWaves, s_round, deepest, bad);
+  else if (lim > kWaves * 64)
+    run = probe_once<2>(sl, mask, hb, lim, s_round[0], deepest, bad);
+  else if (lim > 0)
+    run = probe_once<1>(sl, mask, hb, lim, s_round[0], deepest, bad);
   if (threadIdx.x == 0) {
     if (bad && status) store_agent(status, (int)CASCADE_EINVAL);
     n_prefix_out[i] = run * bt;

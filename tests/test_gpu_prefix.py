@@ -411,11 +411,11 @@ def test_insert_into_reclaimed_sets(dev, per_key, capacity):
 
 @pytest.mark.parametrize("n", [18, 2048, 2049])
 def test_short_prompts(dev, n):
-    """Prompts around 512 blocks, up to which a workgroup's first round looks
-    at 4 x 64 blocks and above at 4 x 256, and runs that end at the edges of
-    the windows."""
+    """Prompts around 256 and 512 blocks, up to which a workgroup looks at
+    4 x 64 and 4 x 128 blocks at once, and runs that end at the edges of the
+    windows."""
     edges = [0, 1, 63, 64, 65, 127, 128, 191, 192, 193, 255, 256, 257, 447, 448, 510, 511, 512]
-    for length in (70, 256, 511, 512, 513):
+    for length in (70, 255, 256, 257, 511, 512, 513):
         entries, reqs = _edge_requests([min(e, length) for e in edges], length, 1_000_000)
         reqs = [reqs[i % len(reqs)] for i in range(n)]
         g, o, _ = run_both(dev, _pw(entries, reqs))
@@ -424,14 +424,16 @@ def test_short_prompts(dev, n):
 
 
 @pytest.mark.parametrize("n", [1, 2500])
-@pytest.mark.parametrize("miss,zero,bad", [
-    (10, 60, True), (10, 64, False), (63, 64, False), (64, 191, True), (191, 192, False),
-    (192, 447, True), (200, 448, False), (255, 447, True), (256, 447, True), (447, 448, False),
-    (448, 499, True), (300, 200, True)])
-def test_zero_hash_past_the_miss_of_a_short_prompt(dev, n, miss, zero, bad):
-    # as for the long prompts above, where the window of the first miss reaches
-    # past the 256 blocks of the first round
-    entries, reqs = _edge_requests([miss], 500, 1_000_000)
+@pytest.mark.parametrize("length,miss,zero,bad", [
+    (500, 10, 60, True), (500, 10, 64, False), (500, 63, 64, False), (500, 64, 191, True),
+    (500, 191, 192, False), (500, 192, 447, True), (500, 200, 448, False), (500, 255, 447, True),
+    (500, 256, 447, True), (500, 447, 448, False), (500, 448, 499, True), (500, 300, 200, True),
+    (250, 63, 64, False), (250, 64, 191, True), (250, 191, 192, False), (250, 192, 249, True),
+    (900, 200, 447, True), (900, 200, 448, False), (900, 500, 703, True), (900, 500, 704, False)])
+def test_zero_hash_past_the_miss_of_a_short_prompt(dev, n, length, miss, zero, bad):
+    # as for the long prompts above, where other windows than those that decide
+    # it are looked up
+    entries, reqs = _edge_requests([miss], length, 1_000_000)
     reqs[0][1][zero] = 0
     reqs += [(64, [5, 6])] * (n - 1)
     d = dev.DevicePrefix(_pw(entries, reqs))
