@@ -1135,11 +1135,11 @@ __global__ __launch_bounds__(kSortBlock) void radix_pass_kernel(
 // seven (eval, prep, one per digit), and nothing in them waits on another
 // workgroup.  There are as many buckets as tiles (p <= kTiledTiles); a bucket
 // holds about T keys, and never more than its samples' gaps and one gap more
-// per tile.  Both
-// sorts are chains of round trips through memory, so fewer launches win: the
-// whole step takes 43.4 us instead of 61.7 at 8192 requests, 49.7 instead of
-// 77.7 at 65536 and 80.4 instead of 122.1 at 262144.  Beyond, a tile would
-// need more than 1024 threads or the samples more than split's registers.
+// per tile.  Both sorts are chains of round trips through memory, so fewer
+// launches win: the whole step takes 39.5 us instead of 61.6 with the radix sort
+// at 8192 requests, 43.9 instead of 76.3 at 65536 and 67 instead of 117 at 262144.
+// Beyond, a tile would need more than 1024 threads or the samples more than
+// split's registers.
 constexpr int kTiledTiles = 256;
 constexpr int kTiledMax = kTiledTiles * 1024;
 // Threads of a bucket's workgroup: twice its usual keys where that fits, so
@@ -2490,7 +2490,7 @@ __device__ __forceinline__ void load_sorted(int n, const Sorted &srt, unsigned (
 // group, the first queued DRAM/NVMe member of a prefix group with a restore
 // want leads and restores under the link cap; every later such member of
 // the group follows and references min(leader's restore, own prefix) blocks
-// of it, taking nothing from the cap).  The last radix pass marks each
+// of it, taking nothing from the cap).  The sort's last launch marks each
 // group's leader position as it writes the order (share_mark: the table
 // holds n - position, 0 for none, so the maximum is the first position);
 // then one launch over the scan tiles (share_kernel) takes the followers'
@@ -3483,7 +3483,10 @@ int step_impl(const cascade_requests_t *rq, const cascade_block_table_t *bt,
   int passes = 1;  // a tiled sort leaves the keys sorted in one move
   if (n <= kTiledMax && range.bits + spec.idx_bits <= 63) {
     // key and index fit one word with the padding above them: the tiled sort.
-    // It clears only the level-1 totals and the scan's words.
+    // It clears only the level-1 totals and the scan's words.  The range of the
+    // keys grows with t_now_ns (waits are bounded by it alone): under an 8B
+    // model's costs they fit up to a clock of 104 h at 8192 requests, 12.7 h at
+    // 65536 and 3 h at 262144.
     spec.lo = (unsigned long long)(range.lo + ((__int128)1 << 61));
     spec.span = (unsigned long long)range.span;
     const int T = L.tile, tiles = L.tiles;
@@ -3509,7 +3512,8 @@ int step_impl(const cascade_requests_t *rq, const cascade_block_table_t *bt,
                        dim3(tiles), dim3(bucket_threads(T)), 0, s, n, tiles, spec.idx_bits, out->info, keys_a,
                        samples, splitters, rec, srt, l1_tot, share ? share_lead : nullptr);
   } else {
-    // longer queues, and parameters that allow wider budgets: the radix sort.
+    // longer queues, and parameters that allow wider budgets (a clock of epoch
+    // nanoseconds among them): the radix sort, 62, 76 and 117 us a step there.
     // Histograms, level-1 totals and the launched passes' look-back words are
     // cleared by eval.
     passes = sort_passes(range.bits);
