@@ -254,7 +254,7 @@ int cascade_step(const cascade_requests_t *requests, const cascade_block_table_t
    HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.
    The same step, on the same kernels, with the same results; the workspace
    is a fixed array inside the library instead of an argument, one per GPU,
-   sized for CASCADE_NOALLOC_MAX_REQUESTS requests (about 45 MB) and held
+   sized for CASCADE_NOALLOC_MAX_REQUESTS requests (about 48 MB) and held
    until the process ends.  The call allocates nothing.  Its first call on a
    device looks up that device's array (the calling thread's current
    device, which must be the stream's), so make that first call outside
