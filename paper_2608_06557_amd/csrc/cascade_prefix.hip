@@ -112,10 +112,15 @@ __global__ __launch_bounds__(kBlock) void index_insert_kernel(IndexSlot *slots, 
   }
 }
 
-// Facts from which on the slot is read first.  Facts that are all known already
-// are faster so from a few thousand on (115000: 4.7 against 11.4 us), new ones only
-// in an index that they fill (520000 into 1 M slots 52 against 60 us, into 4 M 53
-// against 41).  From here on neither is slower than CAS then atomicOr (77 and 53).
+// Facts from which on the slot is read first; half as many in an index of less than
+// four slots a fact, as one built anew has.  Facts that are all known already are
+// faster so from a few thousand on (115000: 4.7 against 11.4 us), new ones where they
+// are many second tiers or fill the index: into an index of twice their number,
+// without and with 30 % second tiers, 262144 facts take 35.7 and 28.6 us (claiming at
+// once 33.7 and 28.9, CAS then atomicOr 39.9 and 29.9), 460000 44.2 and 36.3 (46.8
+// and 49.0; 60.2 and 50.1); into 4 M slots 262144 take 27.2 and 25.0 (20.1 and 22.5;
+// 24.7 and 24.4), 524287 53.2 and 47.4 (40.8 and 46.6; 53.4 and 51.9).  So from here
+// on neither is slower than CAS then atomicOr.
 constexpr int kLookFacts = 1 << 19;
 
 // Lookups per lane in a probe window, at most: the window doubles from 64
@@ -531,7 +536,8 @@ extern "C" int cascade_prefix_index_insert(void *index, int32_t capacity, const 
   if (!index || !capacity_ok(capacity) || ((uintptr_t)index & 15) || n < 0) return CASCADE_EINVAL;
   if (n == 0) return CASCADE_OK;
   if (!hashes || !tiers) return CASCADE_EINVAL;
-  hipLaunchKernelGGL(n < kLookFacts ? index_insert_kernel<false> : index_insert_kernel<true>,
+  const bool look = n >= kLookFacts || (n >= kLookFacts / 2 && capacity / 4 < n);
+  hipLaunchKernelGGL(look ? index_insert_kernel<true> : index_insert_kernel<false>,
                      dim3((n + kBlock - 1) / kBlock), dim3(kBlock), 0,
                      static_cast<hipStream_t>(stream), static_cast<IndexSlot *>(index),
                      (unsigned)(capacity - 1), reinterpret_cast<const unsigned long long *>(hashes),

@@ -305,7 +305,8 @@ def test_insert_contended_and_repeated(dev):
     assert (slots[:, 1][slots[:, 0] == 0] == 0).all()
 
 
-# facts from which on an insert reads a slot before it claims it
+# facts from which on an insert reads a slot before it claims it (half as many
+# in an index of less than four slots a fact)
 LOOK_FACTS = 1 << 19
 
 
@@ -334,13 +335,15 @@ def _assert_contents(dev, index, keys, want):
     assert np.array_equal(got_sets, want[order])
 
 
-@pytest.mark.parametrize("n", [200, 5000, LOOK_FACTS - 1, LOOK_FACTS])
-def test_insert_both_ways(dev, n):
+@pytest.mark.parametrize("n,cap", [
+    (200, 128), (5000, 2048), (LOOK_FACTS // 2 - 1, 1 << 17), (LOOK_FACTS // 2, 1 << 17),
+    (LOOK_FACTS // 2, 1 << 20), (LOOK_FACTS // 2 + 1, 1 << 20), (LOOK_FACTS - 1, 1 << 21),
+    (LOOK_FACTS, 1 << 21)])
+def test_insert_both_ways(dev, n, cap):
     """Several facts per key, most of them on their way at the same time, into
-    a table filled to 9/10, then all of them again."""
-    rng = np.random.default_rng(n)
-    cap = 1 << (max(n // 3, 64) - 1).bit_length()
-    keys = np.unique(rng.integers(1, 1 << 63, int(cap * 0.9), dtype=np.uint64))[:n]
+    a table filled to 9/10 or a large one, then all of them again."""
+    rng = np.random.default_rng(n + cap)
+    keys = np.unique(rng.integers(1, 1 << 63, min(int(cap * 0.9), n // 2), dtype=np.uint64))
     h, t, want = _facts(rng, keys, n)
     index = torch.zeros(cap * 16, dtype=torch.uint8, device="cuda")
     status = torch.zeros(1, dtype=torch.int32, device="cuda")
@@ -375,6 +378,23 @@ def test_inserts_of_both_ways_at_once(dev):
     _assert_contents(dev, index, keys, want)
 
 
+def test_insert_into_emptied_slots_without_a_mark(dev):
+    """Index memory whose emptied slots carry no mark (as a copy of one made
+    otherwise may): the wait for a first tier that will not come ends, and the
+    facts are there all the same."""
+    rng = np.random.default_rng(8)
+    keys = np.unique(rng.integers(1, 1 << 63, 300, dtype=np.uint64))
+    h, t, want = _facts(rng, keys, 900)
+    index = torch.zeros(1024 * 16, dtype=torch.uint8, device="cuda")
+    status = torch.zeros(1, dtype=torch.int32, device="cuda")
+    _insert(dev, index, 1024, h, t, status)
+    index.view(torch.int32)[2::4] = 0                     # every set emptied
+    _insert(dev, index, 1024, h, t, status)
+    torch.cuda.synchronize()
+    assert int(status.item()) == 0
+    _assert_contents(dev, index, keys, want)
+
+
 @pytest.mark.parametrize("per_key,capacity", [(3, 1 << 16), (60, 1 << 20)])
 def test_insert_into_reclaimed_sets(dev, per_key, capacity):
     """Blocks whose last copy a reclamation took come back, beside new blocks
@@ -397,7 +417,7 @@ def test_insert_into_reclaimed_sets(dev, per_key, capacity):
     new = np.setdiff1d(rng.integers(1, 1 << 63, 9000, dtype=np.uint64), keys)
     back = np.concatenate([gone, new])
     n = per_key * len(back)
-    assert (n >= LOOK_FACTS) == (per_key > 3)
+    assert (n >= LOOK_FACTS // 2) == (per_key > 3)
     h, t, want = _facts(rng, back, n)
     _insert(dev, d.index, d.capacity, h, t, d.status)
     torch.cuda.synchronize()
