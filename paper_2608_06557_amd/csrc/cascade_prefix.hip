@@ -371,10 +371,11 @@ __device__ __forceinline__ int probe_once(const uint4 *__restrict__ sl, unsigned
 // short run (most of them) costs one small window, and the wave stops at the
 // first miss: blocks past it in later windows cost nothing.
 // From block kProbeTail on the workgroup's waves share the requests that are left
-// among them, and a workgroup without a prompt that long does not wait for its
-// slowest wave (16384 chat requests 25.1 us, 26.1 with that wait): window after window in one wave, the longest runs (5000 blocks)
-// outlast the rest of the launch.  Chat and agentic prompts, this against every
-// request alone in its wave: 16384 requests 78 against 108 us, 32768 139 against
+// among them: window after window in one wave, the longest runs (5000 blocks)
+// outlast the rest of the launch.  A workgroup without a prompt that long does not
+// wait for its slowest wave (16384 chat requests 25.1 us, 26.1 with that wait).
+// Chat and agentic prompts, this against every request alone in its wave: 16384
+// requests 75 against 103 us, 32768 139 against
 // 181, 65536 191 against 208.  Starting to share at block 960 measured 70, 157
 // and 184 us there, but 700 against 664 us (1984: 660) where half the prompts are
 // long ones and the chip is full without it: the waves' windows past the miss
@@ -565,8 +566,8 @@ extern "C" int cascade_prefix_probe(const void *index, int32_t capacity, int32_t
                        status_dev);
   } else {
     hipLaunchKernelGGL(probe_kernel, dim3((n + kWaves - 1) / kWaves), dim3(kBlock), 0, s, slots,
-                       mask, n, block_offsets, hashes, n_in, block_tokens, n_prefix_out, prefix_tier_out,
-                       status_dev);
+                       mask, n, block_offsets, hashes, n_in, block_tokens, n_prefix_out,
+                       prefix_tier_out, status_dev);
   }
   return hipGetLastError() == hipSuccess ? CASCADE_OK : CASCADE_EHIP;
 }

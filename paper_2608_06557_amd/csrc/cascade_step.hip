@@ -429,8 +429,9 @@ struct KeySpec {
 };
 // Keys sampled from every sorted tile of T keys, at the places j * (T /
 // samples) + the tile's offset.  A bucket's size strays by about 0.3 * (T /
-// samples) * sqrt(tiles) keys, so large tiles take more.  The offset differs from tile to tile, so that tiles holding the
-// same budgets do not all sample the same few of them.
+// samples) * sqrt(tiles) keys, so large tiles take more.  The offset differs from
+// tile to tile, so that tiles holding the same budgets do not all sample the same
+// few of them.
 constexpr int samples_of(int T) { return T > 512 ? 32 : 16; }
 template <int T>
 __device__ __forceinline__ int sample_offset(int tile) {
@@ -2653,9 +2654,10 @@ __global__ __launch_bounds__(kBlock) void share_kernel(int n, int n_tiles, int b
 // of admitted requests, admitted count, held blocks of running prefills left
 // out (all / spill-fits), restored blocks and restoring requests.
 // A tile's level-1 prefix is the sum of the earlier tiles' totals (added by
-// the sort), requested with its sorted records; its level-2
-// prefix comes from the totals that the earlier tiles with grants publish.  Workgroups past the last tile finish the step (victims, slot
-// list, move lists) once every tile has handed over.
+// the sort), requested with its sorted records; its level-2 prefix comes from the
+// totals that the earlier tiles with grants publish.  Workgroups past the last
+// tile finish the step (victims, slot list, move lists) once every tile has
+// handed over.
 __global__ __launch_bounds__(kBlock) void scan_kernel(
     int n, int passes, int n_tiles, Consts c, Ctl *ctl, int *info, Sorted srt,
     const int4 *__restrict__ rec, const int *__restrict__ slots,
@@ -3509,8 +3511,9 @@ int step_impl(const cascade_requests_t *rq, const cascade_block_table_t *bt,
     hipLaunchKernelGGL(T == 256   ? bucket_kernel<256>
                        : T == 512 ? bucket_kernel<512>
                                   : bucket_kernel<1024>,
-                       dim3(tiles), dim3(bucket_threads(T)), 0, s, n, tiles, spec.idx_bits, out->info, keys_a,
-                       samples, splitters, rec, srt, l1_tot, share ? share_lead : nullptr);
+                       dim3(tiles), dim3(bucket_threads(T)), 0, s, n, tiles, spec.idx_bits,
+                       out->info, keys_a, samples, splitters, rec, srt, l1_tot,
+                       share ? share_lead : nullptr);
   } else {
     // longer queues, and parameters that allow wider budgets (a clock of epoch
     // nanoseconds among them): the radix sort, 62, 76 and 117 us a step there.
