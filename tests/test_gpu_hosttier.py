@@ -261,3 +261,56 @@ def test_the_link_leaves_the_gpu_to_others(dev, way):
         best = max(best, beside, key=len)
     assert len(best) >= 4
     assert sorted(best)[len(best) // 2] < 4 * alone
+
+
+def test_captured_restore_and_spill(dev):
+    """Both calls in one captured graph, the copy stream forked and joined by
+    their events: every replay moves the bytes that the buffers hold then, as
+    an eager call does."""
+    import torch
+    from paper_2608_06557_amd import cascade
+    nm, chunk = 25, 4096
+    rng, g, blk, mv, host_off, host_len = _case(77, "layer_major", chunk, nm)
+    pool_len = 2 * g["num_layers"] * g["num_blocks"] * chunk
+    host = torch.zeros(host_len, dtype=torch.uint8).pin_memory()
+    back = torch.zeros(host_len, dtype=torch.uint8).pin_memory()
+    pool = torch.zeros(pool_len, dtype=torch.uint8, device="cuda")
+    st_in = torch.zeros(nm * blk, dtype=torch.uint8, device="cuda")
+    st_out = torch.zeros(nm * blk, dtype=torch.uint8, device="cuda")
+    mv_d = torch.from_numpy(mv.view(np.int32).copy()).cuda()
+    n_d = torch.tensor([nm], dtype=torch.int32, device="cuda")
+    status = torch.zeros(1, dtype=torch.int32, device="cuda")
+    copy_s = torch.cuda.Stream()
+    _, handles = dev.event_handles(3)
+    pl = dev.kv_pool_struct(pool.data_ptr(), g)
+
+    def both():
+        comp_s = torch.cuda.current_stream()
+        for f, st, h in [(cascade.cascade_restore_from_host, st_in, host),
+                         (cascade.cascade_spill_to_host, st_out, back)]:
+            assert f(pl, st.data_ptr(), nm, h.data_ptr(), host_off, mv_d.data_ptr(),
+                     n_d.data_ptr(), nm, 7, status.data_ptr(), copy_s.cuda_stream,
+                     comp_s.cuda_stream, handles) == 0
+        comp_s.wait_stream(copy_s)
+
+    both()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        both()
+    for k in range(4):
+        pool_h = rng.integers(0, 256, pool_len, dtype=np.uint8)
+        host_h = rng.integers(0, 256, host_len, dtype=np.uint8)
+        host.copy_(torch.from_numpy(host_h))
+        pool.copy_(torch.from_numpy(pool_h))
+        back.zero_()
+        torch.cuda.synchronize()
+        graph.replay() if k != 2 else both()      # an eager call between the replays
+        torch.cuda.synchronize()
+        want = pool_h.copy()
+        ref.unpack(want, g, np.concatenate([host_h[o:o + blk] for o in host_off]), mv)
+        assert np.array_equal(pool.cpu().numpy(), want), k
+        for m in range(nm):
+            o = host_off[m]
+            assert np.array_equal(back.numpy()[o:o + blk], host_h[o:o + blk]), (k, m)
+    assert int(status.item()) == 0
